@@ -781,7 +781,7 @@ qf_status qf_qlinear_grouped_fwd(const qf_grouped_desc* d, const int64_t* group_
   QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, g.tile_start, g.order, g.kstart, s),
              "prep"));
   QF_TRY(dev(qf::launch_grouped_nt_rows(d->E, d->T, d->N, d->K, group_offsets, g.tile_start, Aop,
-                                        d->K, Wop, d->K, 0, d->N * d->K, Y, d->N, s),
+                                        d->K, Wop, d->K, d->N * d->K, Y, d->N, s),
              "grouped forward"));
   return ok();
 }
@@ -838,7 +838,7 @@ qf_status qf_qlinear_grouped_bwd_ste(const qf_grouped_desc* d, const int64_t* gr
                  "transpose expert W_hat"));
     }
     QF_TRY(dev(qf::launch_grouped_nt_rows(d->E, d->T, d->K, d->N, group_offsets, g.tile_start, dY,
-                                          d->N, g.whatt, d->N, 0, d->N * d->K, dX, d->K, s,
+                                          d->N, g.whatt, d->N, d->N * d->K, dX, d->K, s,
                                           dyt_by_dx ? g.dyt : nullptr, ldt, g.kstart),
                "grouped dX"));
   }
@@ -1365,7 +1365,7 @@ qf_status qf_qlinear_grouped_lora_fwd(const qf_grouped_desc* d, const qf_lora* l
   QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, g.tile_start, g.order, nullptr, s),
              "prep"));
   QF_TRY(dev(qf::launch_grouped_nt_rows(d->E, d->T, d->N, d->K, group_offsets, g.tile_start, Aop,
-                                        d->K, g.what, d->K, 0, d->N * d->K, Y, d->N, s),
+                                        d->K, g.what, d->K, d->N * d->K, Y, d->N, s),
              "grouped forward"));
   return ok();
 }
@@ -1407,7 +1407,7 @@ qf_status qf_qlinear_grouped_lora_bwd_ste(const qf_grouped_desc* d, const qf_lor
                  "merged quantize (experts, transposed)"));
     }
     QF_TRY(dev(qf::launch_grouped_nt_rows(E, T, K, N, group_offsets, g.tile_start, dY, N, g.whatt,
-                                          N, 0, N * K, dX, K, s),
+                                          N, N * K, dX, K, s),
                "grouped dX"));
   }
   if (!grads) return ok();

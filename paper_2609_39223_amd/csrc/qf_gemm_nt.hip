@@ -7,25 +7,20 @@
 //   dX          = dY W_hat             A = dY [M, N],      B = W_hat^T [K, N]
 //   dW          = dY^T A_hat           A = dY^T [N, M],    B = A_hat^T [K, M]
 //
-// Design (256 x 256 block tile):
-//  - k-contiguous operands (every layer product): 4 wavefronts, one per SIMD, each owning a
-//    128 x 128 sub-tile as 4 x 4 v_mfma_f32_32x32x16_bf16 accumulators (256 AGPRs).  Operands
-//    stored with K as rows: 8 wavefronts, two per SIMD, 128 x 64 each (4 x 2 accumulators).
-//    The bullets below describe the eight-wavefront load split; the four-wavefront form loads
-//    64 rows of both operands per wavefront (see the kernel).
+// Design (256 x 256 block tile, 256 x 128 where that fills the chip better):
+//  - 4 wavefronts, one per SIMD, each owning a 128 x 128 (128 x 64) sub-tile as 16 x 16
+//    v_mfma_f32_16x16x32_bf16 accumulators (256 / 128 AGPRs).
 //  - K advances in 64-deep stages, double-buffered in LDS (2 x 64 KB).  A stage row is 128
 //    bytes, so every global request is a whole 128-byte cache line (32-deep stages fetch half
 //    lines and double the L2 request count).
-//  - Operands move global -> LDS with direct-to-LDS loads (no staging registers, no ds_write):
-//    wavefronts 0-3 load A, 4-7 load B, 8 loads of 8 rows each per wavefront and stage.  The
-//    loads of stage s+1 are spread over four slices (the last of step s-1, right after the
-//    barrier that frees its buffer, and the first two of step s), so the memory pipe sees a
-//    steady stream rather than a burst, and the last of them has a full slice to land.
-//  - Each MFMA is followed by one fragment read for the next slice (and, in three slices of
-//    four, up to one direct-to-LDS load), so the LDS and memory pipes work while the MFMA pipe
-//    is busy.
-//    One barrier per step, before the last slice: it publishes stage s+1 (all loads waited)
-//    and retires every read of stage s (so step s+1 may overwrite that buffer).
+//  - Operands move global -> LDS with direct-to-LDS loads (no staging registers, no ds_write),
+//    16 loads of 8 rows each per wavefront and stage.  The loads of stage s+1 are spread over
+//    two slices (the second of step s-1, right after the barrier that frees its buffer, and the
+//    first of step s), so the memory pipe sees a steady stream rather than a burst.
+//  - MFMAs are interleaved with the fragment reads of the next 32-deep slice and the
+//    direct-to-LDS loads, at most one of each per MFMA, so the LDS and memory pipes work while
+//    the MFMA pipe is busy.  One barrier per step, between its two slices: it publishes stage
+//    s+1 (all loads waited) and retires every read of stage s (so stage s+2 may overwrite it).
 //  - LDS rows hold 64 bf16 (8 chunks of 16 bytes); chunk c of row r sits at slot
 //    c ^ ((r >> 1) & 7), so the 16 rows a fragment read serves in one pass fall on 16
 //    distinct 16-byte bank groups.
@@ -46,156 +41,59 @@
 
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
-#include "qf.h"
-#include "qf_codecs.h"
-#include "qf_internal.h"
+#include "qf_gemm_common.h"
 
 namespace qf {
 namespace {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef short v4i16 __attribute__((ext_vector_type(4)));
-typedef short v8i16 __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int kRow = BK * 2;                     // 128 bytes per LDS row
-constexpr int kOpStage = BM * kRow;              // 32 KB: one operand, one stage
-constexpr int kStage = 2 * kOpStage;             // 64 KB: A then B
-// Dense tile order: groups of kGroupM row tiles, walked column by column (the 9B layer step
-// measured 31.2 / 30.2 / 29.5 / 29.9 / 32.0 / 36.4 ms for groups of 1 / 2 / 4 / 8 / 16 / 32).
-constexpr int kGroupM = 4;
-constexpr int kXcds = 8;
-constexpr int64_t kMaxSplitTiles = 128;          // split tiles of the last round, at most
-constexpr int kPitch16 = BN * 2 + 16;            // epilogue LDS row pitch, bf16 tile (528 B)
-constexpr int kPitch32 = BN * 4 + 32;            // epilogue LDS row pitch, FP32 half tile
-constexpr int kSmemEpi = (BM * kPitch16 > 128 * kPitch32) ? BM * kPitch16 : 128 * kPitch32;
-constexpr int kSmem = (2 * kStage > kSmemEpi) ? 2 * kStage : kSmemEpi;
+constexpr int BM = 256, BN = 256;                // the main tile
 
-// Fragment-major layout of a B operand [N, K] (K a multiple of 16): block (nb, kb) holds rows
-// 32 nb .. 32 nb + 31 and columns 16 kb .. 16 kb + 15 as the 64 lanes' MFMA operands of
-// v_mfma_f32_32x32x16_bf16 (lane L: row 32 nb + L % 32, columns 16 kb + 8 (L / 32) .. +7, 16
-// bytes), blocks ordered nb-major: element (n, k) at
-//   ((n / 32) (K / 16) + k / 16) kBfBlock + ((n % 32) + 32 ((k / 8) % 2)) 8 + k % 8,
-// rows past N zero.  A wavefront's operand of one slice and block is one contiguous 1 KB load.
-constexpr int kBfBlock = 512;                    // elements per block (64 lanes x 8)
-// kDenseAT / kGroupRowsAT: dense / grouped rows, and the launch also writes A^T (NtArgs::at).
-enum Mode { kDense = 0, kGroupRows = 1, kGroupK = 2, kDenseAT = 3, kGroupRowsAT = 4 };
-
-struct NtArgs {
-  const uint16_t* A;
-  const uint16_t* B;
-  void* C;
-  int64_t lda, ldb, ldc;
-  int64_t bstride;        // grouped rows: elements between experts' B
-  int64_t M, N, K;
-  int tiles_m, tiles_n;
-  const int64_t* off;     // grouped rows: [E+1] row offsets
-  const int* tile_start;  // grouped rows: [E+1] per-expert tile prefix
-  int E;
-  // grouped K (per-expert weight gradient): expert e contracts over k in
-  // [BK kstart[e], BK kstart[e+1]) and writes C + e cstride; order[] lists experts by
-  // decreasing work.  Every XCD owns the same contiguous eighth of each expert's tile grid
-  // and runs its share of the experts in that order (see the item mapping in the kernel).
-  const int* kstart;
-  const int* order;
-  int64_t cstride;
-  int vec_store;          // C and ldc allow 16-byte stores
-  // FP32 split of the last partial round.  Tiles [split_from, tiles) are computed as two
-  // K-halves (stages [0, split_stage) and the rest); half h of tile split_from + i writes its
-  // 256 x 256 FP32 partial to part[2 i + h].  Work items are laid out per XCD (each XCD runs
-  // a contiguous range, see remap_xcd): full_per_xcd whole tiles, then split_per_xcd tiles as
-  // 2 halves each, so every XCD ends with a full round of half-length items.
-  float* part;
-  int split_from, full_per_xcd, split_per_xcd;
-  int64_t split_stage;
-  // kDenseAT / kGroupRowsAT: A^T (row stride ldat) is written as a by-product of the main
-  // loop, from the A tiles in LDS (see the kernel).  Dense: A^T [K][M].  Grouped rows: the
-  // padded layout of the grouped weight gradient, expert e's rows at columns 64 kstart[e] + i
-  // and zeros up to 64 kstart[e+1].
-  uint16_t* at;
-  int64_t ldat;
-  // Packed B (the forward's weight, gemm_nt_kernel's BQ != 0): NVFP4 / MXFP4 codes [N][K/2]
-  // (element 2i in the low nibble) and block scales [N][K/16 | K/32], NVFP4's tensor decode
-  // scale S at bq_S; or Q4_K blocks [N][K/256][144] at bq_codes.  Each stage's B tile is
-  // decoded from these in the main loop (K a multiple of 64).
-  const uint8_t* bq_codes;
-  const uint8_t* bq_scales;
-  const float* bq_S;
-};
-
-#define QF_LDS(p) ((__attribute__((address_space(3))) void*)(p))
-
-// 16-byte direct-to-LDS loads: lane l's 16 bytes land at lds + 16 l (lds wave-uniform).
-// The buffer form (buffer_load_dwordx4 ... lds) reads at voff + soff from a resource whose
-// range ends at the operand's last valid byte (reads past it return zeros).  The global form
-// is plain pointer arithmetic, but the compiler counts it as an LDS access of unknown order,
-// which turns the fine-grained lgkmcnt waits of the fragment reads that follow into full
-// waits.  (Plain functions: device builtins with template-dependent operands keep the host
-// pass from emitting the kernel's launch stub.)
-#ifndef QF_NT_GLOBAL_LDS
-#define QF_NT_GLOBAL_LDS 0
-#endif
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int64_t bytes) {
-  const int64_t n = bytes < 0xFFFFFFFFll ? bytes : 0xFFFFFFFFll;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(uint32_t)n,
-                                           0x00020000);
-}
-__device__ __forceinline__ void dma16_buf(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff,
-                                          void* lds) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, QF_LDS(lds), 16, (int)voff, (int)soff, 0, 0);
-}
-__device__ __forceinline__ void dma16_global(const void* g, void* lds) {
-  __builtin_amdgcn_global_load_lds(g, QF_LDS(lds), 16, 0, 0);
+// c += y x^T (16 x 16 x 32).  Inline assembly, because it ties the accumulator to one register:
+// with the builtin the allocator, all 256 accumulation registers in use, moved accumulators
+// through vector registers in the loop (56 moves per 256 MFMAs in the plain form, 580 with
+// spills where the loop also writes A^T); tied, none.  The compiler knows the operands (it waits
+// for the fragment reads) but not that this is an MFMA, so the wait states the hardware wants
+// from software are acc_settle's: two between a vector write of an operand and the MFMA that
+// reads it (fragments come from LDS or memory only, accumulators are initialized before the
+// loop), and those of an eight-pass MFMA between its write and any other read of it.
+__device__ __forceinline__ void mfma16(f32x4_t& c, const bf16x8_t& x, const bf16x8_t& y) {
+  asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(y));
 }
 
-// ds_read_b64_tr_b16 (gfx950): transposing 4 x 16-bit LDS read, see the fragment offsets.
-__device__ __forceinline__ v4i16 lds_tr16(const char* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) v4i16*)(__attribute__((address_space(3))) char*)(p));
+// The wait states between an MFMA and any other access to its result, for the copies the
+// compiler may place where the main loop and its last steps meet.
+__device__ __forceinline__ void mfma_wait() { asm volatile("s_nop 15\n\ts_nop 15"); }
+
+// Pins the accumulators at this point, with wait states after their initialization (BEGIN) or
+// before their first use outside the MFMAs (volatile statements keep their order).
+template <bool BEGIN, int TM, int TN>
+__device__ __forceinline__ void acc_settle(f32x4_t (&acc)[TM][TN]) {
+  if (!BEGIN) mfma_wait();
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+  if (BEGIN) asm volatile("s_nop 7");
 }
 
-// Workgroup barrier that orders LDS accesses only: outstanding global stores are not waited
-// for (a plain __syncthreads() would drain them).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+// f(0), f(1), .. f(N - 1) with compile-time indices (std::integral_constant arguments)
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// 16-byte store of an output row segment.  Output tiles go out non-temporally: they are not
-// read again by this launch, and as ordinary stores their lines displace operand panels in L2
-// (measured 2-5 % slower on whole launches); split partials, read back right away, stay cached.
-__device__ __forceinline__ void store_c16(void* dst, uint4 v, bool nt) {
-  if (nt) __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_t*>(dst));
-  else *reinterpret_cast<uint4*>(dst) = v;
-}
-
-// Two FP32 values -> packed bf16 pair (lo in bits 0-15), round to nearest even.
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  const f32x2_t v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
-
-__device__ __forceinline__ int remap_xcd(int bid, int nb) {
-  const int full = nb - nb % kXcds;
-  if (bid >= full) return bid;
-  return (bid % kXcds) * (full / kXcds) + bid / kXcds;
-}
-
-// WAVES = 8: each wavefront owns a 128 x 64 sub-tile (4 x 2 accumulator blocks) and loads
-// one operand (8 loads per stage); operands stored [K][rows] (A_MN / B_MN) need this form.
-// WAVES = 4: each wavefront owns a 128 x 128 sub-tile (4 x 4 blocks, 256 accumulators in
-// AGPRs) and loads 64 rows of both operands (16 loads per stage); one wavefront per SIMD and a
-// third less LDS fragment traffic per MFMA (0.5 KB instead of 0.75 KB).  Both visit every
-// output element's k slices in the same order, so their results are bit-identical.
+// TM x TN: 16 x 16 accumulator blocks of a wavefront's sub-tile; the 2 x 2 wavefronts of a
+// workgroup own a 32 TM x 32 TN tile (8 x 8: 256 x 256; 8 x 4: 256 x 128).
 //
-// BQ != 0 (QF_FMT_NVFP4 / MXFP4 / Q4K; four wavefronts, dense, k-contiguous, bf16 C): B is the
+// BQ != 0 (QF_FMT_NVFP4 / MXFP4 / Q4K; 256 x 256 tile, dense, bf16 C): B is the
 // packed quantized weight instead of a bf16 matrix.  Each lane owns one B row of its
 // wavefront's 64 (row 64 w + lane) and, one step ahead, loads that row's codes and scales for
 // a stage into registers (32 bytes of codes plus 4 / 2 scale bytes, or the Q4_K block's 16-byte
@@ -204,9 +102,9 @@ __device__ __forceinline__ int remap_xcd(int bid, int nb) {
 // LDS buffer with 16-byte writes, interleaved with that step's MFMAs, before the barrier that
 // publishes the stage.  A keeps its direct-to-LDS loads.
 //
-// BF (four wavefronts, k-contiguous A, dense modes, K a multiple of 64): B comes in the
+// BF (256 x 256 tile, dense modes, K a multiple of 64): B comes in the
 // fragment-major layout (see kBfBlock) straight from memory into the MFMA operand registers,
-// one fully coalesced 1 KB load per 32-row block and 16-deep slice, and never enters LDS: LDS
+// one load of four 256-byte runs per 16-row block and 32-deep slice, and never enters LDS: LDS
 // then carries only A (its direct-to-LDS copies and fragment reads), half of the traffic of
 // the form above, which is the budget the MFMAs wait on.  Each B fragment of stage s+1 is
 // loaded right after the last MFMA that uses the same register for stage s, so it has a whole
@@ -215,43 +113,46 @@ __device__ __forceinline__ int remap_xcd(int bid, int nb) {
 //
 // AT2 (A^T modes): a tile may own two A^T pieces per stage (fewer than 16 tile columns); without
 // it the launch has at least 16 and a tile owns at most one.
-template <bool C_F32, int MODE, bool A_MN, bool B_MN, int WAVES, int BQ = 0, bool BF = false,
-          bool AT2 = false>
-__global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
-  static_assert(WAVES == 8 || (!A_MN && !B_MN), "operands stored [K][rows] need 8 wavefronts");
-  static_assert(BQ == 0 || (WAVES == 4 && MODE == kDense && !C_F32),
-                "packed B: the four-wavefront dense bf16 form");
-  static_assert(!BF || (WAVES == 4 && BQ == 0 && (MODE == kDense || MODE == kDenseAT)),
-                "fragment-major B: the four-wavefront dense forms");
-  constexpr int NJ = WAVES == 8 ? 2 : 4;         // 32-column accumulator blocks per wavefront
-  // direct-to-LDS loads per wavefront per stage (packed or fragment-major B: A's only)
-  constexpr int NLD = (WAVES == 8 || BQ != 0 || BF) ? 8 : 16;
-  // stage s+1's loads: L0 in the last slice of step s-1, L1 in slice 0 and L2 in slice 1
-  // (fragment-major B: all of A's in slice 0)
-  constexpr int L0 = BF ? 0 : NLD == 8 ? 3 : 6, L1 = BF ? 8 : NLD == 8 ? 3 : 5;
-  constexpr int L2 = NLD - L0 - L1;
+template <bool C_F32, int MODE, int TM, int TN, int BQ = 0, bool BF = false, bool AT2 = false,
+          bool PF = false>
+__global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
+  static_assert(TM == 8 && (TN == 8 || TN == 4), "256-row tiles of 256 or 128 columns");
+  static_assert(BQ == 0 || (TN == 8 && MODE == kDense && !C_F32),
+                "packed B: the dense 256 x 256 bf16 form");
+  static_assert(!BF || (TN == 8 && BQ == 0 && (MODE == kDense || MODE == kDenseAT)),
+                "fragment-major B: the dense 256 x 256 forms");
+  constexpr int BM = 32 * TM, BN = 32 * TN;
+  constexpr int kOpStage = BM * kRow;            // A's LDS bytes of a stage; B's follow
+  constexpr int kStage = (BM + BN) * kRow;
+  constexpr int kPitch16 = BN * 2 + 16;          // epilogue LDS row pitch, bf16 tile
+  constexpr int kPitch32 = BN * 4 + 16;          // epilogue LDS row pitch, FP32 half tile
+  constexpr int kMain = 2 * kStage + (PF ? 1024 : 0);   // (the prefetches' landing place)
+  constexpr int kSmem = kMain > BM * kPitch16 ? kMain : BM * kPitch16;
+  static_assert(BM / 2 * kPitch32 <= kSmem, "the FP32 half tile fits the stages' LDS");
+  // direct-to-LDS loads per wavefront per stage: TM of A, then TN of B (packed or
+  // fragment-major B: A's only)
+  constexpr int NLD = (BQ != 0 || BF) ? TM : TM + TN;
   __shared__ __attribute__((aligned(16))) char smem[kSmem];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform (scalar) index
-  const int wm = WAVES == 8 ? w >> 2 : w >> 1, wn = WAVES == 8 ? w & 3 : w & 1;
+  const int wm = w >> 1, wn = w & 1;
   constexpr bool DENSE = MODE == kDense || MODE == kDenseAT;
   constexpr bool AT = MODE == kDenseAT || MODE == kGroupRowsAT;
-  static_assert(!AT || (!C_F32 && WAVES == 4 && !A_MN && !B_MN), "A^T output: bf16 4-wave form");
+  static_assert(!AT || !C_F32, "A^T output: bf16 form");
+  // stage s+1's loads: L0 in the second slice of step s-1, the rest in the first of step s
+  // (fragment-major B: all of A's in the latter)
+  constexpr int L0 = BF ? 0 : AT || BQ != 0 ? NLD / 2 : NLD / 4 * 3;
+  constexpr int CSTEP = TN / 2;                  // MFMAs per copy issued
+  static_assert((L0 > NLD - L0 ? L0 : NLD - L0) * CSTEP <= TM * TN, "a slice holds its copies");
+  // stages between a prefetch and the stage being multiplied: us with 2 / 3 / 4, FP32 6144 x 4096
+  // x 32768 1281 / 1192 / 1171, writing A^T 32768 x 4096 x 24576 4518 / 4561 / 4580, the expert
+  // layer's down projection (forward + backward) 8521 / 8542 / 8646
+  constexpr int kPfDist = DENSE && C_F32 ? 4 : 2;
+  static_assert(!PF || (BQ == 0 && !BF), "prefetch: both operands through LDS");
   const int item = remap_xcd(blockIdx.x, gridDim.x);
   int bid = item, half = -1, pidx = 0;
-  if (DENSE && C_F32 && p.part != nullptr) {
-    const int per_xcd = p.full_per_xcd + 2 * p.split_per_xcd;
-    const int x = item / per_xcd, j = item % per_xcd;
-    if (j < p.full_per_xcd) {
-      bid = x * p.full_per_xcd + j;
-    } else {
-      const int i = x * p.split_per_xcd + ((j - p.full_per_xcd) >> 1);
-      bid = p.split_from + i;
-      half = (j - p.full_per_xcd) & 1;
-      pidx = 2 * i + half;
-    }
-  }
+  if (DENSE && C_F32 && p.part != nullptr) split_item(p, item, bid, half, pidx);
 
   const uint16_t* Bp = p.B;
   int64_t m0, m_end, n0;
@@ -279,13 +180,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
       ks1 = p.kstart[e + 1];
       cofs = (int64_t)e * p.cstride;
     }
-    const int per_group = kGroupM * p.tiles_n;
-    const int g = t / per_group;
-    const int first = g * kGroupM;
-    const int gs = min(p.tiles_m - first, kGroupM);
-    m0 = (int64_t)(first + (t % per_group) % gs) * BM;
+    tile_origin<BM, BN>(p, t, m0, n0);
     m_end = p.M;
-    n0 = (int64_t)((t % per_group) / gs) * BN;
     at_col0 = m0;
     at_end = m_end;
   } else {
@@ -315,59 +211,47 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
   const int64_t n_end = p.N, K = p.K;
 
   // ---- this lane's loads ----------------------------------------------------------------------
-  // WAVES = 8: wavefront w loads operand w >> 2, rows (or k-rows) of quarter w & 3, 8 loads of
-  // 1 KB per stage.  WAVES = 4: wavefront w loads quarter w of both operands, loads 0-7 for A
-  // and 8-15 for B.  Load q of quarter lw at LDS offset op * 32 KB + 8 KB lw + 1 KB (q % 8).
-  // k-major operand ([rows][K], a stage is 256 rows x 128 B): load q covers tile rows
-  // R = 64 lw + 8 (q % 8) .. R + 7, lane l lands at row R + l / 8, slot l % 8 and so fetches
-  // logical chunk (l % 8) ^ ((row >> 1) % 8) = (l % 8) ^ ((4 (q % 2) + l / 16) % 8).
-  // mn-major operand ([K][rows], a stage is 64 k-rows x 512 B): load q covers k-rows
-  // 16 lw + 2 q + {0, 1}; lane l lands at k-row 16 lw + 2 q + l / 32, 16-byte slot l % 32,
-  // and fetches logical chunk (l % 32) ^ (4 (k-row % 4)) (chunk c = columns 8c..8c+7).
-  const int lw = WAVES == 8 ? w & 3 : w;
-  const int wop = WAVES == 8 ? w >> 2 : 0;       // WAVES = 8: this wavefront's operand
-  auto op_of = [&](int q) { return WAVES == 8 ? wop : q >> 3; };
+  // Wavefront w loads rows 8 TM w .. of A (loads 0 .. TM - 1, 8 rows = 1 KB each) and rows 8 TN w
+  // .. of B (loads TM ..).  A stage is BM + BN rows of 128 bytes: load q covers 8 rows from R,
+  // lane l lands at row R + l / 8, slot l % 8 and so fetches logical chunk
+  // (l % 8) ^ ((row >> 1) % 8) = (l % 8) ^ ((4 (q % 2) + l / 16) % 8).
   const char* gb[2];
   __amdgpu_buffer_rsrc_t rs[2];
-  int64_t sstride = kRow;                        // bytes from one stage to the next
   uint32_t goff[NLD];
-  bool mn = false;
 #pragma unroll
   for (int op = 0; op < 2; ++op) {
-    if (WAVES == 8 && op != wop) continue;       // uniform
     if ((BQ != 0 || BF) && op == 1) continue;    // packed / fragment-major B: registers
-    const bool omn = op ? B_MN : A_MN;
     const int64_t ld = op ? p.ldb : p.lda;
     const int64_t r0 = op ? n0 : m0;
-    const int64_t rlim = (op ? n_end : m_end) - r0 - 1;   // last valid row (k-major) / column
-    if (!omn) {
-      gb[op] = reinterpret_cast<const char*>((op ? Bp : p.A) + r0 * ld);
-      rs[op] = make_rsrc(gb[op], (rlim * ld + K) * 2);
+    const int64_t rlim = (op ? n_end : m_end) - r0 - 1;   // last valid row
+    gb[op] = reinterpret_cast<const char*>((op ? Bp : p.A) + r0 * ld);
+    rs[op] = make_rsrc(gb[op], (rlim * ld + K) * 2);
+    const int nq = op ? TN : TM, q0 = op ? TM : 0;
 #pragma unroll
-      for (int q = 0; q < NLD; ++q) {
-        if (WAVES == 4 && (q >> 3) != op) continue;
-        const int qq = q & 7;
-        const int64_t row = lw * 64 + qq * 8 + (lane >> 3);
-        const int64_t rc = row < rlim ? row : rlim;
-        const int c = (lane & 7) ^ ((4 * (qq & 1) + (lane >> 4)) & 7);
-        goff[q] = (uint32_t)((rc * ld + c * 8) * 2);
-      }
-    } else {
-      mn = true;
-      gb[op] = reinterpret_cast<const char*>((op ? Bp : p.A) + r0);
-      rs[op] = make_rsrc(gb[op], ((K - 1) * ld + rlim + 1) * 2);
-      sstride = (int64_t)BK * ld * 2;
-      const int clim = (int)(rlim / 8);          // last chunk holding valid columns
-#pragma unroll
-      for (int q = 0; q < NLD; ++q) {
-        const int kr = lw * 16 + q * 2 + (lane >> 5);
-        int c = (lane & 31) ^ (4 * (kr & 3));
-        c = c < clim ? c : clim;
-        goff[q] = (uint32_t)(((int64_t)kr * ld + c * 8) * 2);
-      }
+    for (int q = 0; q < nq; ++q) {
+      const int64_t row = (w * nq + q) * 8 + (lane >> 3);
+      const int64_t rc = row < rlim ? row : rlim;
+      const int c = (lane & 7) ^ ((4 * (q & 1) + (lane >> 4)) & 7);
+      goff[q0 + q] = (uint32_t)((rc * ld + c * 8) * 2);
     }
   }
-  auto lds_of = [&](int q) { return op_of(q) * kOpStage + lw * 8192 + (q & 7) * 1024; };
+  // ---- L2 prefetch (PF) -------------------------------------------------------------------
+  // pf_off: this lane's 16 bytes of one eighth of A's rows and two of one quarter of B's rows of
+  // a stage (the tiles of an XCD that run together share them, see the main loop).
+  uint32_t pf_off[3];
+  if (PF) {
+    const int64_t ra = m_end - m0 - 1, rb = n_end - n0 - 1;
+    const int64_t a = ((n0 / BN) & 7) * (BM / 8) + w * (BM / 32) + (lane >> 3);
+    pf_off[0] = (uint32_t)(((a < ra ? a : ra) * p.lda + (lane & 7) * 8) * 2);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t b = ((m0 / BM) & 3) * (BN / 4) + w * (BN / 16) + h * 8 + (lane >> 3);
+      pf_off[1 + h] = (uint32_t)(((b < rb ? b : rb) * p.ldb + (lane & 7) * 8) * 2);
+    }
+  }
+  auto lds_of = [&](int q) {
+    return q < TM ? (w * TM + q) * 1024 : kOpStage + (w * TN + q - TM) * 1024;
+  };
 
   // ---- packed B (BQ != 0): this lane's row and its per-stage loads -------------------------
   // Row brow = 64 w + lane of the tile (rows past N decode the last valid row; their outputs
@@ -378,7 +262,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
     uint4 c0, c1, hd;
     uint32_t sc;
   };
-  const int brow = lw * 64 + lane;
+  const int brow = w * 64 + lane;
   const uint8_t* bq_row = nullptr;
   const uint8_t* bq_srow = nullptr;
   float bq_S = 0.0f;
@@ -439,12 +323,13 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
                               ((c ^ ((brow >> 1) & 7)) << 4)) = make_uint4(o[0], o[1], o[2], o[3]);
   };
   BqRegs bq_cur{}, bq_nxt{};
-  // The main loop decodes a stage as a chain of small operations, one after each MFMA of the
-  // step's first three slices, so that no gap between two MFMAs holds more than a few VALU
-  // instructions (one wavefront per SIMD: nothing else issues while this one decodes).
+  // The main loop decodes a stage as a chain of small operations, each after an MFMA of its own
+  // (the first half of the chunks in the second slice of the step before, the rest in the first
+  // slice), so that no gap between two MFMAs holds more than a few VALU instructions (one
+  // wavefront per SIMD: nothing else issues while this one decodes).
   //   NVFP4, 48 operations: per chunk c, the block decode scale D (even c), the four element
   //          pairs (E2M1 -> FP32, x D, bf16 pack), the 16-byte LDS write.
-  //   MXFP4, 24 (every other MFMA): per chunk, pairs 0-1 with the E8M0 scale, pairs 2-3, the
+  //   MXFP4, 24: per chunk, pairs 0-1 with the E8M0 scale, pairs 2-3, the
   //          NaN-block select and the write.
   //   Q4_K, 43: the super-block's d and dmin, the two sub-blocks' step t1 and offset t2, then
   //          per chunk four element pairs (the first also extracts the chunk's nibbles) and
@@ -541,53 +426,43 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
   };
 
   // ---- fragment offsets ----------------------------------------------------------------------
-  // k-major: slice kk, fragment i at fo[kk] + i * 4096 (32 rows of 128 bytes); fragment rows
-  // start 32-aligned, so the swizzle term (row >> 1) & 7 is (lane >> 1) & 7.
-  // mn-major: two ds_read_b64_tr_b16 per fragment (k 0-3 and 4-7 of the lane's 8).  Within
-  // each group of 16 lanes that instruction hands output lane L element j of source lane
-  // 4 j + L / 4 (element L % 4), so source lane 4 j + a points at k-row kb + j, columns
-  // c0 + 4 a .. +3: output lane L then holds k-rows kb .. kb+3 of column c0 + L.  Lane l
-  // (group g = l / 16) serves MFMA lane rows 16 (g % 2) + L and k-half g / 2; fragment f's base
-  // is fo[f], plus (16 kk + 4 h) * 512 bytes for slice kk, half h.
-  int foa[4], fob[4];
+  // 32-deep slice kk, fragment i (16 rows of 128 bytes): lane l holds row l % 16, columns
+  // 8 (l / 16) .. +7 of the slice, at fo[kk] + i * 2048; fragment rows start 16-aligned, so the
+  // swizzle term (row >> 1) & 7 is (lane >> 1) & 7.
+  int foa[2], fob[2];
   {
-    const int ra = wm * 128 + (lane & 31), rb = wn * (NJ * 32) + (lane & 31);
+    const int ra = wm * (16 * TM) + (lane & 15), rb = wn * (16 * TN) + (lane & 15);
     const int sw = (lane >> 1) & 7;
-    const int g = lane >> 4, j = (lane >> 2) & 3, a = lane & 3;
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const int c = 2 * x + (lane >> 5);
-      // mn-major fragment x: columns start at (wm * 128 or wn * 64) + 32 x
-      const int rowj = 8 * (g >> 1) + j;
-      if (A_MN) foa[x] = rowj * 512 + ((4 * ((wm * 4 + x) ^ j) + 2 * (g & 1) + (a >> 1)) << 4) + 8 * (a & 1);
-      else foa[x] = ra * kRow + ((c ^ sw) << 4);
-      if (B_MN) fob[x] = kOpStage + rowj * 512 + ((4 * ((wn * NJ + x) ^ j) + 2 * (g & 1) + (a >> 1)) << 4) + 8 * (a & 1);
-      else fob[x] = kOpStage + rb * kRow + ((c ^ sw) << 4);
+    for (int x = 0; x < 2; ++x) {
+      const int c = 4 * x + (lane >> 4);
+      foa[x] = ra * kRow + ((c ^ sw) << 4);
+      fob[x] = kOpStage + rb * kRow + ((c ^ sw) << 4);
     }
   }
 
-  f32x16_t acc[4][NJ];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x16_t{};
-  bf16x8_t fa[2][4], fb[2][NJ];
-  // Fragment-major B (BF): fbr[kk][j] holds the B fragment of 16-deep slice kk and 32-row
-  // block j of this wavefront's 128 columns for the stage in use.  Block j's fragments start at
-  // bf_base[j]; slice kk of global stage se is kBfBlock elements further per (4 se + kk).
-  bf16x8_t fbr[BF ? 4 : 1][BF ? 4 : 1];
-  const uint16_t* bf_base[BF ? 4 : 1];
+  f32x4_t acc[TM][TN];
+  bf16x8_t fa[2][TM], fb[2][TN];
+  // Fragment-major B (BF): fbr[kk][j] holds the B fragment of 32-deep slice kk and 16-row
+  // block j of this wavefront's 128 columns for the stage in use.  Blocks 2 jj and 2 jj + 1 are
+  // the halves of the layout's 32-row block jj, whose fragments start at bf_base[jj]; slice kk
+  // of global stage se is kBfBlock elements further per 16 columns, i.e. per (4 se + 2 kk).
+  bf16x8_t fbr[BF ? 2 : 1][BF ? TN : 1];
+  const uint16_t* bf_base[BF ? TN / 2 : 1];
   if (BF) {
     const int64_t nblocks = (p.N + 31) / 32, kblocks = p.K / 16;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int64_t nb = (n0 + wn * 128) / 32 + j;
+    for (int jj = 0; jj < TN / 2; ++jj) {
+      int64_t nb = (n0 + wn * 128) / 32 + jj;
       nb = nb < nblocks ? nb : nblocks - 1;      // blocks past N: outputs never stored
-      bf_base[j] = p.B + (nb * kblocks) * kBfBlock + lane * 8;
+      bf_base[jj] = p.B + (nb * kblocks + (lane >> 5)) * kBfBlock +
+                    ((lane & 15) + 32 * ((lane >> 4) & 1)) * 8;
     }
   }
   auto bf_load = [&](int64_t se, int kk, int j) __attribute__((always_inline)) {
-    if (BF) fbr[kk][j] = *reinterpret_cast<const bf16x8_t*>(bf_base[j] + (se * 4 + kk) * kBfBlock);
+    if (BF)
+      fbr[kk][j] = *reinterpret_cast<const bf16x8_t*>(bf_base[j >> 1] + (se * 4 + 2 * kk) * kBfBlock +
+                                                      (j & 1) * 128);
   };
 
   // K order: the stages of this item's range [ks0, ks1) are visited rotated by an offset that
@@ -606,35 +481,23 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
     const int se = s + krot;
     return se >= ks1 ? se - klen : se;
   };
-  const uint32_t sstride32 = (uint32_t)sstride;
   // load q of global stage se into buffer buf
   auto dma = [&](int se, int buf, int q) __attribute__((always_inline)) {
-    char* l = smem + buf * kStage + lds_of(q);
-    const int op = op_of(q);
-    if (QF_NT_GLOBAL_LDS) dma16_global(gb[op] + (int64_t)se * sstride + goff[q], l);
-    else dma16_buf(rs[op], goff[q], (uint32_t)se * sstride32, l);
+    dma16_buf(rs[q < TM ? 0 : 1], goff[q], (uint32_t)se * (uint32_t)kRow,
+              smem + buf * kStage + lds_of(q));
   };
-  // Fragment read r of a slice, in the order the slice's MFMAs consume them: A0, B0, B1, A1..A3.
-  auto frag = [&](const char* st, int kk, int f, bool is_b) __attribute__((always_inline)) -> bf16x8_t {
-    const bool mnf = is_b ? B_MN : A_MN;
-    if (!mnf) {
-      const int* fo = is_b ? fob : foa;
-      return *reinterpret_cast<const bf16x8_t*>(st + fo[kk] + f * 4096);
-    }
-    const char* base = st + (is_b ? fob[f] : foa[f]) + kk * 16 * 512;
-    const v4i16 lo = lds_tr16(base);
-    const v4i16 hi = lds_tr16(base + 4 * 512);
-    const v8i16 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8_t, v);
-  };
+  // Fragment read r of a slice, in the order the slice's MFMAs consume them: A0, B0 .., A1 ...
   auto read_one = [&](const char* st, int kk, int r, bf16x8_t* a, bf16x8_t* b) __attribute__((always_inline)) {
-    if (r == 0) a[0] = frag(st, kk, 0, false);
-    else if (r <= NJ) { if (!BF) b[r - 1] = frag(st, kk, r - 1, true); }
-    else a[r - NJ] = frag(st, kk, r - NJ, false);
+    if (r == 0 || r > TN) {
+      const int i = r == 0 ? 0 : r - TN;
+      a[i] = *reinterpret_cast<const bf16x8_t*>(st + foa[kk] + i * 2048);
+    } else if (!BF) {
+      b[r - 1] = *reinterpret_cast<const bf16x8_t*>(st + fob[kk] + (r - 1) * 2048);
+    }
   };
   auto read_all = [&](const char* st, int kk, bf16x8_t* a, bf16x8_t* b) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < 4 + NJ; ++r) read_one(st, kk, r, a, b);
+    for (int r = 0; r < TM + TN; ++r) read_one(st, kk, r, a, b);
   };
   // ---- A^T output (kDenseAT, kGroupRowsAT) ---------------------------------------------------
   // A stage's A^T is 16 pieces: piece u is k columns 4 u .. 4 u + 3 over the tile's 256 rows, so
@@ -719,131 +582,124 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
     __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 2);   // non-temporal
   };
   constexpr bool at_two = AT && AT2;             // a second piece per stage is possible
-  // One 16-deep slice of MFMAs from (a, b), with the fragment reads of the next slice (from
-  // rst / rkk into ra, rb) and, if LOADS, the direct-to-LDS loads of global stage ls into
-  // buffer lbuf, issued one per MFMA.  The scheduling fences keep that interleave.
-  // extra(t) runs after MFMA t (the A^T reads and stores, the packed-B decode, index updates).
+  // One 32-deep slice of TM TN MFMAs from (a, b), with the fragment reads of the next slice (from
+  // rst / rkk into ra, rb), one after each MFMA from the first, and, if LOADS, the direct-to-LDS
+  // loads [qa, qa + nq) of global stage ls into buffer lbuf, one per CSTEP MFMAs.
+  // The scheduling fences keep that interleave.  extra(t) runs after MFMA t (the A^T reads and
+  // stores, the packed-B decode, index updates).
   auto slice = [&](auto reads, auto loads, const bf16x8_t* a, const bf16x8_t* b,
                    const char* rst, int rkk, bf16x8_t* ra, bf16x8_t* rb, int ls, int lbuf,
                    int qa, int nq, auto extra) __attribute__((always_inline)) {
     constexpr bool READS = decltype(reads)::value, LOADS = decltype(loads)::value;
-    constexpr int NM = 4 * NJ, NR = 4 + NJ;
-#pragma unroll
-    for (int t = 0; t < NM; ++t) {
-      acc[t / NJ][t % NJ] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[t % NJ], a[t / NJ],
-                                                                    acc[t / NJ][t % NJ], 0, 0, 0);
+    constexpr int NM = TM * TN, NR = TM + TN;
+    static_for<NM>([&](auto ti) __attribute__((always_inline)) {
+      constexpr int t = decltype(ti)::value;
+      mfma16(acc[t / TN][t % TN], b[t % TN], a[t / TN]);
       __builtin_amdgcn_sched_barrier(0);
-      if (READS && t < NR) read_one(rst, rkk, t, ra, rb);
-      if (LOADS) {
-        // loads [qa, qa + nq) of stage ls, one per MFMA from the first
-        if (t < nq) dma(ls, lbuf, qa + t);
+      if constexpr (READS && t < NR) read_one(rst, rkk, t, ra, rb);
+      if constexpr (LOADS && t % CSTEP == 1) {
+        if (t / CSTEP < nq) dma(ls, lbuf, qa + t / CSTEP);
       }
       extra(t);
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
   };
-  // Loads are spread over the step: stage s+1's loads go out L0 in the last slice of step s-1
-  // (right after its barrier freed stage s-1's buffer), L1 in slice 0 and L2 in slice 1 of
-  // step s; the barrier before slice 3 waits for them.  A step knows the global stages of
-  // loop stages s and s+1 (e_cur, e_nx1, handed on by the step before) and works out that of
-  // s+2 (e_nx2) in a free slot of slice 2.  LD1 / LD2: loop stages s+1 / s+2 exist (no copies
-  // are issued for stages past the end, so the epilogue does not wait for any).  cur: the
+  // A step computes loop stage s in two slices.  The barrier between them publishes stage s+1
+  // (its loads waited) and retires every read of stage s, whose buffer then takes stage s+2's
+  // loads: L0 of them in this step's second slice, the rest in the next step's first.  A step
+  // knows the global stages of loop stages s and s+1 (e_cur, e_nx1, handed on by the step before)
+  // and works out that of s+2 (e_nx2) in a free slot.  LD1 / LD2: loop stages s+1 / s+2 exist (no
+  // copies are issued for stages past the end, so the epilogue does not wait for any).  cur: the
   // buffer holding stage s.
   int e_cur = 0, e_nx1 = 0;
   auto step = [&](int s, int s_end, auto last, auto ld1, auto ld2, int cur)
       __attribute__((always_inline)) {
     constexpr bool LAST = decltype(last)::value, LD1 = decltype(ld1)::value;
     constexpr bool LD2 = decltype(ld2)::value;
+    constexpr int NM = TM * TN;
+    constexpr bool PFS = PF && LD1 && LD2;
     const int nxt = cur ^ 1;
     const char* cs = smem + cur * kStage;
-    // packed or fragment-major B use stage s+2's index from slice 0 on
-    constexpr bool EARLY = BQ != 0 || BF;
     int e_nx2 = 0;
     auto calc_nx2 = [&]() __attribute__((always_inline)) {
       e_nx2 = gstage(s + 2 < s_end ? s + 2 : s_end - 1);
     };
-    if (EARLY) calc_nx2();
+    if (BQ != 0) calc_nx2();                     // (its registers are loaded early in slice 0)
     // A^T modes: this tile's A^T pieces of the stage (u0 and, with fewer than 16 tile columns,
-    // u0 + tiles_n; >= 16: none) are read in slice 1, while the stage is resident, and stored
-    // in slice 3, after the barrier; at_u then moves on to stage s+1's piece.
+    // u0 + tiles_n; >= 16: none) are read in slice 0, while the stage is resident, and stored
+    // in slice 1, after the barrier; at_u then moves on to stage s+1's piece.
     const int u0 = at_u, u1 = at_u + p.tiles_n;
     u32x4_t v0 = {0, 0, 0, 0}, v1 = {0, 0, 0, 0};
     u32x2_t w0 = {0, 0}, w1 = {0, 0};
     // the main loop's stores cover a full stage (kvalid = BK) of A^T rows
     __amdgpu_buffer_rsrc_t at_rs;
     const char* at_base = nullptr;
+    // (slot numbers are for TN = 8, 64 MFMAs a slice; half of them with TN = 4)
+    constexpr int H = NM / 32;
+    auto at_hook0 = [&](int t) __attribute__((always_inline)) {
+      if (!AT) return;
+      if (t == 16 * H + 1) at_read2(cur, u0 & 15, 0, v0);
+      if (t == 17 * H + 1) at_read2(cur, u0 & 15, 2, v0);
+      if (at_two && t == 18 * H + 1) at_read2(cur, u1 & 15, 0, v1);
+      if (at_two && t == 19 * H + 1) at_read2(cur, u1 & 15, 2, v1);
+      if (t == 22 * H + 1)
+        at_base = reinterpret_cast<const char*>(p.at) + (uint64_t)(uint32_t)e_cur * at_sbytes;
+      if (t == 24 * H + 1) at_rs = make_rsrc(at_base, (int64_t)at_sbytes);
+    };
     auto at_hook1 = [&](int t) __attribute__((always_inline)) {
       if (!AT) return;
-      if (t == 8) at_read2(cur, u0 & 15, 0, v0);
-      if (t == 9) at_read2(cur, u0 & 15, 2, v0);
-      if (at_two && t == 10) at_read2(cur, u1 & 15, 0, v1);
-      if (at_two && t == 11) at_read2(cur, u1 & 15, 2, v1);
-    };
-    auto at_hook2 = [&](int t) __attribute__((always_inline)) {
-      if (AT && t == 12)
-        at_base = reinterpret_cast<const char*>(p.at) + (uint64_t)(uint32_t)e_cur * at_sbytes;
-      if (AT && t == 13) at_rs = make_rsrc(at_base, (int64_t)at_sbytes);
-    };
-    auto at_hook3 = [&](int t) __attribute__((always_inline)) {
-      if (!AT) return;
-      if (t == 8) w0 = at_pack(v0);
-      if (t == 9) at_put(at_rs, u0, w0);
-      if (at_two && t == 10) w1 = at_pack(v1);
-      if (at_two && t == 11) at_put(at_rs, u1, w1);
-      if (!LAST && t == 13) {
+      if (t == 18 * H + 1) w0 = at_pack(v0);
+      if (t == 20 * H + 1) at_put(at_rs, u0, w0);
+      if (at_two && t == 22 * H + 1) w1 = at_pack(v1);
+      if (at_two && t == 24 * H + 1) at_put(at_rs, u1, w1);
+      if (!LAST && t == 27 * H + 1) {
         int u = e_nx1 == ks0 ? at_u_wrap : at_u - at_d;
         at_u = u < 0 ? u + p.tiles_n : u;
       }
     };
-    // Packed B: stage s+2's registers are loaded in slice 0 (they have the rest of the step,
-    // up to the barrier's wait), and stage s+1's (loaded one step earlier) are decoded into
-    // buffer nxt in small operations spread over slices 0-2.
-    // slot g (0..47) = the MFMA of slices 0-2 that the operation follows
-    auto bq_slot = [&](int g) __attribute__((always_inline)) {
-      if (BQ != 0) {
-        if (g == 1) bq_load(e_nx2, bq_nxt);
-        if (BQ == QF_FMT_MXFP4) {
-          if ((g & 1) == 0 && g / 2 < kBqOps) bq_op(bq_cur, e_nx1, g / 2, nxt);
-        } else if (g < kBqOps) {
-          bq_op(bq_cur, e_nx1, g, nxt);
-        }
-      }
-    };
-    // Fragment-major B: after MFMA t = 12 + j of slice kk (the last one using fbr[kk][j]), that
-    // register is loaded with stage s+1's fragment (not in the last step).
+    // Packed B: stage s+2's registers are loaded early in slice 0 (they have until the barrier's
+    // wait); stage s+1's second half is decoded into buffer nxt in slice 0, stage s+2's first
+    // half into buffer cur in slice 1 (slot g of 24: the g-th decode operation of the half).
+    constexpr int kBqHalf = BQ == QF_FMT_NVFP4 ? 24 : BQ == QF_FMT_MXFP4 ? 12 : 23;
     auto bf_hook = [&](int kk, int t) __attribute__((always_inline)) {
-      if (BF && !LAST && t >= 12) bf_load(e_nx1, kk, t - 12);
+      // after MFMA t = NM - TN + j, the last one using fbr[kk][j], that register is loaded with
+      // stage s+1's fragment (not in the last step)
+      if (BF && !LAST && t >= NM - TN) bf_load(e_nx1, kk, t - (NM - TN));
     };
     auto hook0 = [&](int t) __attribute__((always_inline)) {
-      bq_slot(t);
+      if (BQ != 0) {
+        if (t == 1) bq_load(e_nx2, bq_nxt);
+        const int g = t / 2 + kBqHalf;
+        if (LD1 && t % 2 == 0 && g < kBqOps) bq_op(bq_cur, e_nx1, g, nxt);
+      }
+      at_hook0(t);
+      if (BQ == 0 && t == 15 * H + 1) calc_nx2();
+      constexpr int P0 = 17 * H, PS = 2 * H;
+      if (PFS && (t == P0 || t == P0 + PS || t == P0 + 2 * PS)) {
+        const int q = (t - P0) / PS;
+        const int e1 = e_nx2 + (kPfDist - 2), e = e1 >= ks1 ? e1 - klen : e1;
+        dma16_buf(rs[q ? 1 : 0], pf_off[q], (uint32_t)e * (uint32_t)kRow, smem + 2 * kStage);
+      }
       bf_hook(0, t);
     };
     auto hook1 = [&](int t) __attribute__((always_inline)) {
-      bq_slot(16 + t);
+      if (BQ != 0) {
+        const int g = t / 2;
+        if (LD2 && t % 2 == 0 && g < kBqHalf) bq_op(bq_cur, e_nx2, g, cur);
+      }
       at_hook1(t);
       bf_hook(1, t);
     };
-    auto hook2 = [&](int t) __attribute__((always_inline)) {
-      bq_slot(32 + t);
-      at_hook2(t);
-      if (!EARLY && t == 2 * NJ + 1) calc_nx2();   // a free slot (slices hold 4 NJ MFMAs)
-      bf_hook(2, t);
-    };
-    auto hook3 = [&](int t) __attribute__((always_inline)) {
-      at_hook3(t);
-      bf_hook(3, t);
-    };
     slice(std::true_type{}, std::integral_constant<bool, LD1>{}, fa[0], BF ? fbr[0] : fb[0], cs,
-          1, fa[1], fb[1], e_nx1, nxt, L0, L1, hook0);
-    slice(std::true_type{}, std::integral_constant<bool, LD1>{}, fa[1],
-          BF ? fbr[1 % (BF ? 4 : 1)] : fb[1], cs, 2, fa[0], fb[0], e_nx1, nxt, L0 + L1, L2, hook1);
-    slice(std::true_type{}, std::false_type{}, fa[0], BF ? fbr[2 % (BF ? 4 : 1)] : fb[0], cs, 3,
-          fa[1], fb[1], 0, 0, 0, 0, hook2);
+          1, fa[1], fb[1], e_nx1, nxt, L0, NLD - L0, hook0);
     if (BF && !LAST) {
-      // A's copies of stage s+1 and everything before them; the 12 B loads issued after them in
-      // slices 0-2 stay in flight (vmcnt(12); expcnt not waited; lgkmcnt(0): this wavefront's
-      // reads of stage s are done before the barrier lets stage s+2's copies overwrite it)
-      __builtin_amdgcn_s_waitcnt(12 | (7 << 4) | (0 << 8));
+      // A's copies of stage s+1 and everything before them; the TN B loads issued after them in
+      // this slice stay in flight (expcnt not waited; lgkmcnt(0): this wavefront's reads of
+      // stage s are done before the barrier lets stage s+2's copies overwrite it)
+      __builtin_amdgcn_s_waitcnt(8 | (7 << 4) | (0 << 8));
+    } else if (PFS) {
+      // the three prefetches stay in flight (vmcnt(3), the rest as above)
+      __builtin_amdgcn_s_waitcnt(3 | (7 << 4) | (0 << 8));
     } else {
       __builtin_amdgcn_s_waitcnt(0);
     }
@@ -851,8 +707,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
     __builtin_amdgcn_sched_barrier(0);
     if (BQ != 0) bq_cur = bq_nxt;               // complete: the wait above covered its loads
     slice(std::integral_constant<bool, !LAST>{}, std::integral_constant<bool, LD2>{}, fa[1],
-          BF ? fbr[3 % (BF ? 4 : 1)] : fb[1], smem + nxt * kStage, 0, fa[0], fb[0], e_nx2, cur, 0,
-          L0, hook3);
+          BF ? fbr[BF ? 1 : 0] : fb[1], smem + nxt * kStage, 0, fa[0], fb[0], e_nx2, cur, 0, L0,
+          hook1);
     e_cur = e_nx1;
     e_nx1 = e_nx2;
   };
@@ -866,23 +722,36 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
     e_nx1 = gstage(s0 + 1 < s1 ? s0 + 1 : s1 - 1);
 #pragma unroll
     for (int q = 0; q < NLD; ++q) dma(e_cur, 0, q);
+    if (s0 + 1 < s1) {
+#pragma unroll
+      for (int q = 0; q < L0; ++q) dma(e_nx1, 1, q);
+    }
     if (BF) {
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
+      for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) bf_load(e_cur, kk, j);
+        for (int j = 0; j < TN; ++j) bf_load(e_cur, kk, j);
     }
+  }
+  // (the accumulators are cleared while the first copies are under way)
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{};
+  acc_settle<true>(acc);
+  if (s1 > s0) {
     if (BQ != 0) {
-      // stage s0's B decoded now; stage s0+1's registers for the first step
+      // stage s0's B decoded now, and the first half of stage s0+1's operations
       BqRegs first;
       bq_load(e_cur, first);
       bq_load(e_nx1, bq_cur);
 #pragma unroll
       for (int c = 0; c < 8; ++c) bq_decode(first, e_cur, c, 0);
-    }
-    if (s0 + 1 < s1) {
+      if (s0 + 1 < s1) {
+        constexpr int kBqHalf = BQ == QF_FMT_NVFP4 ? 24 : BQ == QF_FMT_MXFP4 ? 12 : 23;
 #pragma unroll
-      for (int q = 0; q < L0; ++q) dma(e_nx1, 1, q);
+        for (int u = 0; u < kBqHalf; ++u) bq_op(bq_cur, e_nx1, u, 1);
+      }
     }
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_s_barrier();
@@ -892,21 +761,26 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
     if (AT) at_u = at_first(e_cur);
     const std::true_type T{};
     const std::false_type F{};
-    if (WAVES == 4) {
-      // two steps per iteration: with one loop-carried copy of the 256 accumulators the
-      // register allocator keeps them in place (a one-step loop body rotates them through
-      // other AGPRs at every back edge)
-      for (; s + 3 < s1; s += 2) {
-        step(s, s1, F, T, T, 0);
-        step(s + 1, s1, F, T, T, 1);
-      }
+    // two steps per iteration: with one loop-carried copy of the 256 accumulators the register
+    // allocator keeps them in place (a one-step loop body rotates them through other AGPRs at
+    // every back edge)
+    for (; s + 3 < s1; s += 2) {
+      step(s, s1, F, T, T, 0);
+      step(s + 1, s1, F, T, T, 1);
     }
-    for (; s + 2 < s1; ++s) step(s, s1, F, T, T, (s - s0) & 1);
+    mfma_wait();
+    if (s + 2 < s1) {
+      step(s, s1, F, T, T, 0);
+      mfma_wait();
+      ++s;
+    }
     if (s + 1 < s1) {
       step(s, s1, F, T, F, (s - s0) & 1);
+      mfma_wait();
       ++s;
     }
     step(s, s1, T, F, F, (s - s0) & 1);
+    mfma_wait();
   }
   if (krem > 0) {
     // Partial last stage: masked loads through registers into buffer 0.  The wait + barrier
@@ -916,15 +790,10 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int q = 0; q < NLD; ++q) {
-      bool valid;
-      if (!mn) {
-        const int c = (lane & 7) ^ ((4 * (q & 1) + (lane >> 4)) & 7);
-        valid = nfull * BK + c * 8 < K;
-      } else {
-        valid = nfull * BK + lw * 16 + q * 2 + (lane >> 5) < K;
-      }
+      const int c = (lane & 7) ^ ((4 * (q & 1) + (lane >> 4)) & 7);
       uint4 v = make_uint4(0, 0, 0, 0);
-      if (valid) v = *reinterpret_cast<const uint4*>(gb[op_of(q)] + nfull * sstride + goff[q]);
+      if (nfull * BK + c * 8 < K)
+        v = *reinterpret_cast<const uint4*>(gb[q < TM ? 0 : 1] + nfull * kRow + goff[q]);
       *reinterpret_cast<uint4*>(smem + lds_of(q) + lane * 16) = v;
     }
     __syncthreads();
@@ -933,24 +802,25 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
         at_store(nfull, (int)krem, u, at_read(smem, u));
     }
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      if (kk * 16 >= krem) break;                // uniform: the rest of the stage is zeros
+    for (int kk = 0; kk < 2; ++kk) {
+      if (kk * 32 >= krem) break;                // uniform: the rest of the stage is zeros
       read_all(smem, kk, fa[0], fb[0]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[0][j], fa[0][i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < TN; ++j)
+          mfma16(acc[i][j], fb[0][j], fa[0][i]);
     }
   }
 
+  acc_settle<false>(acc);
+
   // ---- epilogue: the tile goes through LDS and leaves as whole-row 16-byte stores ----------
   // Each MFMA takes the B fragment as its first operand, so accumulator block (i, j) holds the
-  // transposed product: element v sits at row lane % 32 of the block and column
-  // 8 (v / 4) + 4 (lane / 32) + v % 4, i.e. a lane owns four consecutive columns of one row per
-  // group v / 4, written to LDS with one 8-byte (bf16) or 16-byte (FP32) store.
+  // transposed product: lane l owns columns 4 (l / 16) .. +3 of row l % 16 of the block, written
+  // to LDS with one 8-byte (bf16) or 16-byte (FP32) store.
   __syncthreads();                               // every wavefront is done with the operands
-  // Destination: the output tile, or (split halves) a dense 256 x 256 FP32 partial.
+  // Destination: the output tile, or (split halves) a dense BM x BN FP32 partial.
   char* Cp = reinterpret_cast<char*>(p.C) + cofs * (C_F32 ? 4 : 2);
   int64_t ldc = p.ldc, em0 = m0, em_end = m_end, en0 = n0, en_end = n_end;
   int vec = p.vec_store;
@@ -958,75 +828,39 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
     Cp = reinterpret_cast<char*>(p.part + (int64_t)pidx * BM * BN);
     ldc = BN; em0 = 0; em_end = BM; en0 = 0; en_end = BN; vec = 1;
   }
-  const int er = wm * 128 + (lane & 31);          // this lane's row in block (0, *)
-  const int ec = wn * (NJ * 32) + 4 * (lane >> 5);  // its first column in block (*, 0), group 0
+  const int ec = wn * (16 * TN) + 4 * (lane >> 4);  // this lane's first column in block (*, 0)
   if (!C_F32) {
     // bf16 pairs by the hardware pack (round to nearest even; a NaN result stays a quiet NaN)
+    const int er = wm * (16 * TM) + (lane & 15);    // its row in block (0, *)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x16_t& a = acc[i][j];
-          const uint2 w = make_uint2(pack_bf16x2(a[4 * g], a[4 * g + 1]),
-                                     pack_bf16x2(a[4 * g + 2], a[4 * g + 3]));
-          *reinterpret_cast<uint2*>(smem + (er + 32 * i) * kPitch16 + (ec + 32 * j + 8 * g) * 2) = w;
-        }
-    lds_barrier();
-    const int c8 = (tid & 31) * 8;
-    const int64_t gcol = en0 + c8;
-    constexpr int kRowsPerPass = WAVES * 64 / 32;  // 32 lanes cover a row
-#pragma unroll 4
-    for (int it = 0; it < BM / kRowsPerPass; ++it) {
-      const int r = it * kRowsPerPass + (tid >> 5);
-      const int64_t grow = em0 + r;
-      if (grow >= em_end || gcol >= en_end) continue;
-      const uint4 v = *reinterpret_cast<const uint4*>(smem + r * kPitch16 + c8 * 2);
-      uint16_t* dst = reinterpret_cast<uint16_t*>(Cp) + grow * ldc + gcol;
-      if (vec && gcol + 8 <= en_end) {
-        store_c16(dst, v, half < 0);
-      } else {
-        const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-        for (int e = 0; e < 8 && gcol + e < en_end; ++e)
-          dst[e] = (uint16_t)(wv[e >> 1] >> (16 * (e & 1)));
+      for (int j = 0; j < TN; ++j) {
+        const f32x4_t& a = acc[i][j];
+        *reinterpret_cast<uint2*>(smem + (er + 16 * i) * kPitch16 + (ec + 16 * j) * 2) =
+            make_uint2(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));
       }
-    }
+    lds_barrier();
+    store_rows16<BM, BN, kPitch16, 256>(smem, Cp, ldc, em0, em_end, en0, en_end, vec);
   } else {
-    // FP32 tile (256 KB) in two halves: in half h every wavefront writes its row blocks 2h and
-    // 2h + 1, so LDS row q (0..127) holds tile row (q / 64) * 128 + 64 h + q % 64.
-    const int c4 = (tid & 63) * 4;
-    const int64_t gcol = en0 + c4;
+    // FP32 tile in two halves: in half h every wavefront writes its row blocks 4 h .. 4 h + 3, so
+    // LDS row q (0..127) holds tile row (q / 64) * 128 + 64 h + q % 64.
+    constexpr int HB = TM / 2;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       if (h) lds_barrier();                      // half 0 has been read out of LDS
 #pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
+      for (int ii = 0; ii < HB; ++ii)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const f32x16_t& a = acc[2 * h + ii][j];
-            const int q = wm * 64 + ii * 32 + (lane & 31);
-            *reinterpret_cast<float4*>(smem + q * kPitch32 + (ec + 32 * j + 8 * g) * 4) =
-                make_float4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
-          }
-      lds_barrier();
-      constexpr int kRowsPerPass32 = WAVES;       // 64 lanes cover a row
-#pragma unroll 4
-      for (int it = 0; it < 128 / kRowsPerPass32; ++it) {
-        const int q = it * kRowsPerPass32 + (tid >> 6);
-        const int64_t grow = em0 + (q >> 6) * 128 + 64 * h + (q & 63);
-        if (grow >= em_end || gcol >= en_end) continue;
-        const uint4 v = *reinterpret_cast<const uint4*>(smem + q * kPitch32 + c4 * 4);
-        float* dst = reinterpret_cast<float*>(Cp) + grow * ldc + gcol;
-        if (vec && gcol + 4 <= en_end) {
-          store_c16(dst, v, half < 0);
-        } else {
-          const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-          for (int e = 0; e < 4 && gcol + e < en_end; ++e) dst[e] = __uint_as_float(wv[e]);
+        for (int j = 0; j < TN; ++j) {
+          const f32x4_t& a = acc[HB * h + ii][j];
+          const int q = wm * (16 * HB) + ii * 16 + (lane & 15);
+          *reinterpret_cast<float4*>(smem + q * kPitch32 + (ec + 16 * j) * 4) =
+              make_float4(a[0], a[1], a[2], a[3]);
         }
-      }
+      lds_barrier();
+      store_rows32<BN, kPitch32, 256>(smem, Cp, ldc, em0, em_end, en0, en_end, vec, half < 0,
+                                      [&](int q) { return (q >> 6) * 128 + 64 * h + (q & 63); });
     }
   }
 }
@@ -1037,12 +871,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_nt_kernel(NtArgs p) {
 __global__ __launch_bounds__(256) void split_reduce_kernel(NtArgs p) {
   const int i = blockIdx.y;
   const int t = p.split_from + i;
-  const int per_group = kGroupM * p.tiles_n;
-  const int g = t / per_group;
-  const int first = g * kGroupM;
-  const int gs = min(p.tiles_m - first, kGroupM);
-  const int64_t m0 = (int64_t)(first + (t % per_group) % gs) * BM;
-  const int64_t n0 = (int64_t)((t % per_group) / gs) * BN;
+  int64_t m0, n0;
+  tile_origin<BM, BN>(p, t, m0, n0);
   const int e = (blockIdx.x * 256 + threadIdx.x) * 4;      // element of the 256 x 256 tile
   const int r = e / BN, c = e % BN;
   const int64_t grow = m0 + r, gcol = n0 + c;
@@ -1089,6 +919,23 @@ size_t gemm_nt_split_bytes(int64_t M, int64_t N) {
 
 namespace {
 
+// Launches with at least this many stages prefetch operands into L2 (see the kernel).  Long
+// contractions read panels that no earlier round of tiles has left in the last-level cache: us,
+// without -> with, at 4096 x 4096 x 32768 841 -> 750 (FP32 out), 24576 x 4096 x 32768 4660 -> 4530
+// (FP32), 8192 x 4096 x 14336 651 -> 622, 32768 x 4096 x 6144 (writing A^T) 1144 -> 1130.  Short
+// ones find theirs there and only pay for the extra requests: 8192 x 14336 x 4096 617 -> 630.
+constexpr int64_t kPfMinStages = 96;
+
+// The dense k-contiguous launch with 32 TN columns per tile.
+template <int TN, bool PF>
+void launch_form(const NtArgs& a, int c_f32, bool at, dim3 grid, hipStream_t s) {
+  const dim3 b(256);
+  if (c_f32) hipLaunchKernelGGL((gemm_nt_kernel<true, kDense, 8, TN, 0, false, false, PF>), grid, b, 0, s, a);
+  else if (at && a.tiles_n < 16) hipLaunchKernelGGL((gemm_nt_kernel<false, kDenseAT, 8, TN, 0, false, true, PF>), grid, b, 0, s, a);
+  else if (at) hipLaunchKernelGGL((gemm_nt_kernel<false, kDenseAT, 8, TN, 0, false, false, PF>), grid, b, 0, s, a);
+  else hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, 8, TN, 0, false, false, PF>), grid, b, 0, s, a);
+}
+
 // Shared launch of the dense NT GEMM: bf = B in the fragment-major layout (a_mn = b_mn = 0,
 // K a multiple of 64).
 hipError_t launch_dense(int64_t M, int64_t N, int64_t K, const uint16_t* A, int64_t lda, int a_mn,
@@ -1100,9 +947,16 @@ hipError_t launch_dense(int64_t M, int64_t N, int64_t K, const uint16_t* A, int6
     return hipErrorInvalidValue;
   if (bf && (a_mn || b_mn || K % BK != 0 || reinterpret_cast<uintptr_t>(B) % 16 != 0))
     return hipErrorInvalidValue;
+  // A last round of 256 x 256 tiles that would leave at least half the CUs idle runs as K-halves
+  // instead (FP32 output only; needs a partial buffer and at least two full stages).  The split is
+  // decided per XCD: each runs tiles / 8 tiles on cus / 8 CUs.
+  const int64_t cus = resident_blocks();
+  const int64_t t256 = ((M + BM - 1) / BM) * ((N + BN - 1) / BN), rem = t256 % cus;
+  const bool halves = c_f32 && part != nullptr && t256 % kXcds == 0 && cus % kXcds == 0 &&
+                      rem > 0 && 2 * rem <= cus && rem <= kMaxSplitTiles && K / BK >= 2;
   if (at != nullptr && (N == 0 || (N + BN - 1) / BN < 8)) {
-    // no tiles, or fewer than 8 tile columns (a tile would own more than two A^T pieces per
-    // stage): the transpose kernel writes A^T instead
+    // no tiles, or fewer than 8 tile columns (a tile would own more than two
+    // A^T pieces per stage): the transpose kernel writes A^T instead
     if (M > 0 && K > 0) {
       const hipError_t e = launch_transpose_bf16(A, M, K, lda, at, ldat, 1, 0, 0, s);
       if (e != hipSuccess) return e;
@@ -1116,42 +970,30 @@ hipError_t launch_dense(int64_t M, int64_t N, int64_t K, const uint16_t* A, int6
   a.M = M; a.N = N; a.K = K;
   a.at = at; a.ldat = ldat;
   a.vec_store = vec_store_ok(C, ldc, c_f32 ? 4 : 2);
+  if (halves) a.split_stage = (K / BK) / 2;
+  const bool pf = K / BK >= kPfMinStages;
   a.tiles_m = (int)((M + BM - 1) / BM);
   a.tiles_n = (int)((N + BN - 1) / BN);
   const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
   int64_t items = tiles;
-  // A last round that would leave at least half the CUs idle runs as K-halves instead (FP32
-  // output only; needs a partial buffer and at least two full stages).
-  // The split is decided per XCD: each runs tiles / 8 tiles on cus / 8 CUs.
-  const int64_t cus = resident_blocks();
-  const int64_t rem = tiles % cus;
-  if (c_f32 && part != nullptr && tiles % kXcds == 0 && cus % kXcds == 0 && rem > 0 &&
-      2 * rem <= cus && rem <= kMaxSplitTiles && K / BK >= 2) {
+  if (halves) {
     a.part = part;
     a.split_from = (int)(tiles - rem);
     a.full_per_xcd = (int)((tiles - rem) / kXcds);
     a.split_per_xcd = (int)(rem / kXcds);
-    a.split_stage = (K / BK) / 2;
     items = tiles + rem;
   }
-  const dim3 grid((unsigned)items);
-  const dim3 b8(8 * 64), b4(4 * 64);
-  if (bf) {
-    if (c_f32) hipLaunchKernelGGL((gemm_nt_kernel<true, kDense, false, false, 4, 0, true>), grid, b4, 0, s, a);
-    else if (at != nullptr) hipLaunchKernelGGL((gemm_nt_kernel<false, kDenseAT, false, false, 4, 0, true, true>), grid, b4, 0, s, a);
-    else hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, false, false, 4, 0, true>), grid, b4, 0, s, a);
-  } else if (c_f32) {
-    if (a_mn && b_mn) hipLaunchKernelGGL((gemm_nt_kernel<true, kDense, true, true, 8>), grid, b8, 0, s, a);
-    else if (b_mn) hipLaunchKernelGGL((gemm_nt_kernel<true, kDense, false, true, 8>), grid, b8, 0, s, a);
-    else if (a_mn) hipLaunchKernelGGL((gemm_nt_kernel<true, kDense, true, false, 8>), grid, b8, 0, s, a);
-    else hipLaunchKernelGGL((gemm_nt_kernel<true, kDense, false, false, 4>), grid, b4, 0, s, a);
+  const dim3 grid((unsigned)items), b(256);
+  if (a_mn || b_mn) {
+    const hipError_t e = launch_gemm_mn_tiles(a, (int)items, a_mn, b_mn, c_f32, s);
+    if (e != hipSuccess) return e;
+  } else if (bf) {
+    if (c_f32) hipLaunchKernelGGL((gemm_nt_kernel<true, kDense, 8, 8, 0, true>), grid, b, 0, s, a);
+    else if (at != nullptr) hipLaunchKernelGGL((gemm_nt_kernel<false, kDenseAT, 8, 8, 0, true, true>), grid, b, 0, s, a);
+    else hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, 8, 8, 0, true>), grid, b, 0, s, a);
   } else {
-    if (a_mn && b_mn) hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, true, true, 8>), grid, b8, 0, s, a);
-    else if (b_mn) hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, false, true, 8>), grid, b8, 0, s, a);
-    else if (a_mn) hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, true, false, 8>), grid, b8, 0, s, a);
-    else if (at != nullptr && a.tiles_n < 16) hipLaunchKernelGGL((gemm_nt_kernel<false, kDenseAT, false, false, 4, 0, false, true>), grid, b4, 0, s, a);
-    else if (at != nullptr) hipLaunchKernelGGL((gemm_nt_kernel<false, kDenseAT, false, false, 4>), grid, b4, 0, s, a);
-    else hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, false, false, 4>), grid, b4, 0, s, a);
+    if (pf) launch_form<8, true>(a, c_f32, at != nullptr, grid, s);
+    else launch_form<8, false>(a, c_f32, at != nullptr, grid, s);
   }
   if (a.part != nullptr)
     hipLaunchKernelGGL(split_reduce_kernel, dim3(BM * BN / (256 * 4), (unsigned)rem), dim3(256),
@@ -1221,16 +1063,16 @@ hipError_t launch_gemm_nt_packed_b(int64_t M, int64_t N, int64_t K, const uint16
   a.vec_store = vec_store_ok(C, ldc, 2);
   a.tiles_m = (int)((M + BM - 1) / BM);
   a.tiles_n = (int)((N + BN - 1) / BN);
-  const dim3 grid((unsigned)((int64_t)a.tiles_m * a.tiles_n)), b4(4 * 64);
+  const dim3 grid((unsigned)((int64_t)a.tiles_m * a.tiles_n)), b4(256);
   switch (bfmt) {
     case QF_FMT_NVFP4:
-      hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, false, false, 4, QF_FMT_NVFP4>), grid, b4, 0, s, a);
+      hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, 8, 8, QF_FMT_NVFP4>), grid, b4, 0, s, a);
       break;
     case QF_FMT_MXFP4:
-      hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, false, false, 4, QF_FMT_MXFP4>), grid, b4, 0, s, a);
+      hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, 8, 8, QF_FMT_MXFP4>), grid, b4, 0, s, a);
       break;
     case QF_FMT_Q4K:
-      hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, false, false, 4, QF_FMT_Q4K>), grid, b4, 0, s, a);
+      hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, 8, 8, QF_FMT_Q4K>), grid, b4, 0, s, a);
       break;
     default:
       return hipErrorInvalidValue;
@@ -1240,14 +1082,14 @@ hipError_t launch_gemm_nt_packed_b(int64_t M, int64_t N, int64_t K, const uint16
 
 hipError_t launch_grouped_nt_rows(int64_t E, int64_t T, int64_t N, int64_t K, const int64_t* off,
                                   const int* tile_start, const uint16_t* A, int64_t lda,
-                                  const uint16_t* B, int64_t ldb, int b_mn, int64_t bstride,
+                                  const uint16_t* B, int64_t ldb, int64_t bstride,
                                   uint16_t* C, int64_t ldc, hipStream_t s, uint16_t* at,
                                   int64_t ldat, const int* kstart) {
-  if (at != nullptr && (b_mn || (N + BN - 1) / BN < 8 || kstart == nullptr || ldat % 4 != 0 ||
+  if (at != nullptr && ((N + BN - 1) / BN < 8 || kstart == nullptr || ldat % 4 != 0 ||
                         ldat >= kGemmAtMaxLd || reinterpret_cast<uintptr_t>(at) % 8 != 0))
     return hipErrorInvalidValue;
   if (T == 0 || N == 0 || E == 0) return hipSuccess;
-  if (!nt_offsets_fit(K, lda, ldb, false, b_mn)) return hipErrorInvalidValue;
+  if (!nt_offsets_fit(K, lda, ldb)) return hipErrorInvalidValue;
   NtArgs a{};
   a.A = A; a.B = B; a.C = C; a.lda = lda; a.ldb = ldb; a.ldc = ldc; a.bstride = bstride;
   a.M = T; a.N = N; a.K = K; a.off = off; a.tile_start = tile_start; a.E = (int)E;
@@ -1257,10 +1099,9 @@ hipError_t launch_grouped_nt_rows(int64_t E, int64_t T, int64_t N, int64_t K, co
   a.tiles_m = (int)((T + BM - 1) / BM + E);
   const int64_t per = ((int64_t)a.tiles_m * a.tiles_n + kXcds - 1) / kXcds;
   const dim3 grid((unsigned)(kXcds * per));
-  if (b_mn) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRows, false, true, 8>), grid, dim3(8 * 64), 0, s, a);
-  else if (at != nullptr && a.tiles_n < 16) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRowsAT, false, false, 4, 0, false, true>), grid, dim3(4 * 64), 0, s, a);
-  else if (at != nullptr) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRowsAT, false, false, 4>), grid, dim3(4 * 64), 0, s, a);
-  else hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRows, false, false, 4>), grid, dim3(4 * 64), 0, s, a);
+  if (at != nullptr && a.tiles_n < 16) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRowsAT, 8, 8, 0, false, true, true>), grid, dim3(256), 0, s, a);
+  else if (at != nullptr) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRowsAT, 8, 8, 0, false, false, true>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRows, 8, 8, 0, false, false, true>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1278,7 +1119,7 @@ hipError_t launch_grouped_nt_k(int64_t E, int64_t M, int64_t N, int64_t Kpad, co
   a.tiles_n = (int)((N + BN - 1) / BN);
   const int64_t cmax = ((int64_t)a.tiles_m * a.tiles_n + kXcds - 1) / kXcds;
   const dim3 grid((unsigned)(kXcds * E * cmax));
-  hipLaunchKernelGGL((gemm_nt_kernel<true, kGroupK, false, false, 4>), grid, dim3(4 * 64), 0, s, a);
+  hipLaunchKernelGGL((gemm_nt_kernel<true, kGroupK, 8, 8, 0, false, false, true>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
