@@ -59,6 +59,7 @@ struct NtArgs {
   // 2 halves each, so every XCD ends with a full round of half-length items.
   float* part;
   int split_from, full_per_xcd, split_per_xcd;
+  int norot;              // walk K from its start on every XCD (see the kernel's K order)
   int64_t split_stage;
   // kDenseAT / kGroupRowsAT: A^T (row stride ldat) is written as a by-product of the main
   // loop, from the A tiles in LDS (see the kernel).  Dense: A^T [K][M].  Grouped rows: the
@@ -204,5 +205,10 @@ __device__ __forceinline__ void store_rows32(const char* smem, char* Cp, int64_t
 // qf_gemm_mn.hip: `items` work items of 256 x 256 tiles with at least one K-as-rows operand.
 hipError_t launch_gemm_mn_tiles(const NtArgs& a, int items, int a_mn, int b_mn, int c_f32,
                                 hipStream_t s);
+
+// Tiles of the dense k-contiguous product: the main kernel's two (qf_gemm_nt.hip) and the small
+// kernel's (qf_gemm_small.hip).  All but k256x256 walk K from its start (NtArgs::norot).
+enum class GemmTile { k256x256, k256x128, k128x128, k128x64, k64x64, k32x32, k16x16 };
+hipError_t launch_gemm_small(const NtArgs& a, GemmTile form, int c_f32, hipStream_t s);
 
 }  // namespace qf

@@ -9,7 +9,10 @@
 //
 // Design (256 x 256 block tile, 256 x 128 where that fills the chip better):
 //  - 4 wavefronts, one per SIMD, each owning a 128 x 128 (128 x 64) sub-tile as 16 x 16
-//    v_mfma_f32_16x16x32_bf16 accumulators (256 / 128 AGPRs).
+//    v_mfma_f32_16x16x32_bf16 accumulators (256 / 128 AGPRs).  What bounds the full launches is
+//    power: the chip holds 1.97 GHz in a loop of these against 1.70 GHz in one of
+//    32 x 32 x 16 MFMAs, so 8192 x 14336 x 4096 takes 617 us (1.56 PFLOP/s) against 664 with the
+//    same loop built on the latter, to the same bits.
 //  - K advances in 64-deep stages, double-buffered in LDS (2 x 64 KB).  A stage row is 128
 //    bytes, so every global request is a whole 128-byte cache line (32-deep stages fetch half
 //    lines and double the L2 request count).
@@ -19,7 +22,8 @@
 //    first of step s), so the memory pipe sees a steady stream rather than a burst.
 //  - MFMAs are interleaved with the fragment reads of the next 32-deep slice and the
 //    direct-to-LDS loads, at most one of each per MFMA, so the LDS and memory pipes work while
-//    the MFMA pipe is busy.  One barrier per step, between its two slices: it publishes stage
+//    the MFMA pipe is busy (copies every second or third MFMA instead of every fourth: 2 to 6 %
+//    slower launches).  One barrier per step, between its two slices: it publishes stage
 //    s+1 (all loads waited) and retires every read of stage s (so stage s+2 may overwrite it).
 //  - LDS rows hold 64 bf16 (8 chunks of 16 bytes); chunk c of row r sits at slot
 //    c ^ ((r >> 1) & 7), so the 16 rows a fragment read serves in one pass fall on 16
@@ -475,7 +479,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
   if (half == 1) ks0 = (int)p.split_stage;
   if (half == 0) ks1 = (int)p.split_stage;
   const int klen = ks1 > ks0 ? ks1 - ks0 : 1;
-  const int krot = (int)(blockIdx.x % kXcds) * (klen / kXcds);
+  const int krot = p.norot ? 0 : (int)(blockIdx.x % kXcds) * (klen / kXcds);
   // global stage of loop stage s
   auto gstage = [&](int s) __attribute__((always_inline)) -> int {
     const int se = s + krot;
@@ -926,6 +930,36 @@ namespace {
 // ones find theirs there and only pay for the extra requests: 8192 x 14336 x 4096 617 -> 630.
 constexpr int64_t kPfMinStages = 96;
 
+// The tile of a dense k-contiguous product: the one whose busiest compute unit copies the fewest
+// operand bytes, ceil(tiles / units) (rows + columns), the smaller tile of equals (the figures are
+// at the top of qf_gemm_small.hip; 2048 x 4096 x 4096: 84 us in 256 x 256 tiles, 71 in 256 x 128).
+// It depends on M, N and the device alone, so every form of one product (A^T written or not, B
+// packed, in fragment order) sums in the same order.
+// halves: FP32 output summed as two K halves; 256 x 256 tiles then run as twice as many half-length
+// items plus a pass that adds them (2048 x 2048 x 4096: 63 us, 41 in 128 x 128 tiles that add the
+// halves themselves), and the 256 x 128 tile, which does not form halves, is left out.
+GemmTile gemm_tile(int64_t M, int64_t N, bool halves = false) {
+  static constexpr struct { GemmTile t; int m, n; } kTiles[] = {
+      {GemmTile::k256x256, 256, 256}, {GemmTile::k256x128, 256, 128},
+      {GemmTile::k128x128, 128, 128}, {GemmTile::k128x64, 128, 64},
+      {GemmTile::k64x64, 64, 64},     {GemmTile::k32x32, 32, 32},
+      {GemmTile::k16x16, 16, 16}};
+  const int64_t cus = resident_blocks();
+  GemmTile best = GemmTile::k256x256;
+  int64_t cost = INT64_MAX;
+  for (const auto& c : kTiles) {
+    const int64_t tiles = ((M + c.m - 1) / c.m) * ((N + c.n - 1) / c.n);
+    int64_t v = (tiles + cus - 1) / cus * (c.m + c.n);
+    if (halves && c.t == GemmTile::k256x128) continue;
+    if (halves && c.t == GemmTile::k256x256) v = tiles > cus ? 0 : v / 2 + 64;
+    if (v <= cost) {
+      cost = v;
+      best = c.t;
+    }
+  }
+  return best;
+}
+
 // The dense k-contiguous launch with 32 TN columns per tile.
 template <int TN, bool PF>
 void launch_form(const NtArgs& a, int c_f32, bool at, dim3 grid, hipStream_t s) {
@@ -954,8 +988,12 @@ hipError_t launch_dense(int64_t M, int64_t N, int64_t K, const uint16_t* A, int6
   const int64_t t256 = ((M + BM - 1) / BM) * ((N + BN - 1) / BN), rem = t256 % cus;
   const bool halves = c_f32 && part != nullptr && t256 % kXcds == 0 && cus % kXcds == 0 &&
                       rem > 0 && 2 * rem <= cus && rem <= kMaxSplitTiles && K / BK >= 2;
-  if (at != nullptr && (N == 0 || (N + BN - 1) / BN < 8)) {
-    // no tiles, or fewer than 8 tile columns (a tile would own more than two
+  const bool nt = !a_mn && !b_mn;
+  const GemmTile tile = nt ? gemm_tile(M, N, halves) : GemmTile::k256x256;
+  const bool large = bf || tile == GemmTile::k256x256 || tile == GemmTile::k256x128;
+  const int tn = !bf && tile == GemmTile::k256x128 ? 4 : 8;   // 32-column blocks of a tile
+  if (at != nullptr && (N == 0 || !large || (N + 32 * tn - 1) / (32 * tn) < 8)) {
+    // no tiles, the small kernel, or fewer than 8 tile columns (a tile would own more than two
     // A^T pieces per stage): the transpose kernel writes A^T instead
     if (M > 0 && K > 0) {
       const hipError_t e = launch_transpose_bf16(A, M, K, lda, at, ldat, 1, 0, 0, s);
@@ -971,9 +1009,11 @@ hipError_t launch_dense(int64_t M, int64_t N, int64_t K, const uint16_t* A, int6
   a.at = at; a.ldat = ldat;
   a.vec_store = vec_store_ok(C, ldc, c_f32 ? 4 : 2);
   if (halves) a.split_stage = (K / BK) / 2;
+  if (!large) return launch_gemm_small(a, tile, c_f32, s);
   const bool pf = K / BK >= kPfMinStages;
+  a.norot = tile != GemmTile::k256x256;
   a.tiles_m = (int)((M + BM - 1) / BM);
-  a.tiles_n = (int)((N + BN - 1) / BN);
+  a.tiles_n = (int)((N + 32 * tn - 1) / (32 * tn));
   const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
   int64_t items = tiles;
   if (halves) {
@@ -991,6 +1031,9 @@ hipError_t launch_dense(int64_t M, int64_t N, int64_t K, const uint16_t* A, int6
     if (c_f32) hipLaunchKernelGGL((gemm_nt_kernel<true, kDense, 8, 8, 0, true>), grid, b, 0, s, a);
     else if (at != nullptr) hipLaunchKernelGGL((gemm_nt_kernel<false, kDenseAT, 8, 8, 0, true, true>), grid, b, 0, s, a);
     else hipLaunchKernelGGL((gemm_nt_kernel<false, kDense, 8, 8, 0, true>), grid, b, 0, s, a);
+  } else if (tn == 4) {
+    if (pf) launch_form<4, true>(a, c_f32, at != nullptr, grid, s);
+    else launch_form<4, false>(a, c_f32, at != nullptr, grid, s);
   } else {
     if (pf) launch_form<8, true>(a, c_f32, at != nullptr, grid, s);
     else launch_form<8, false>(a, c_f32, at != nullptr, grid, s);
@@ -1063,6 +1106,7 @@ hipError_t launch_gemm_nt_packed_b(int64_t M, int64_t N, int64_t K, const uint16
   a.vec_store = vec_store_ok(C, ldc, 2);
   a.tiles_m = (int)((M + BM - 1) / BM);
   a.tiles_n = (int)((N + BN - 1) / BN);
+  a.norot = gemm_tile(M, N) != GemmTile::k256x256;
   const dim3 grid((unsigned)((int64_t)a.tiles_m * a.tiles_n)), b4(256);
   switch (bfmt) {
     case QF_FMT_NVFP4:

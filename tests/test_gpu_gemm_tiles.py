@@ -1,7 +1,8 @@
-"""The dense GEMM in full grids, ragged in both directions, over contraction depths below one stage,
-of whole stages and with a partial last stage; contractions long enough for the L2 prefetch; the
-FP32 split of the last round; and the forms that must agree bit for bit (A^T written along, weight
-decoded inside) at such shapes.
+"""The dense GEMM's tiles: one shape per tile of the choice (the smallest ceil(tiles / 256) (rows +
+columns) on the 256-unit device), each ragged in both directions, over contraction depths below
+one stage, at whole stage groups, with a partial last group and a partial last stage; contractions
+long enough for the L2 prefetch; the FP32 split of the last round; and the forms that must agree
+bit for bit (A^T written along, weight decoded inside) at shapes that run in the large tiles.
 Expected values are FP64 products, tolerance the layer's (bf16 rounding of the result)."""
 import numpy as np
 import pytest
@@ -42,11 +43,12 @@ def _check(qf, M, N, K, c32, ws=None):
     assert_close(g, oracle.linear_fwd(np.ascontiguousarray(A[rows]), B), f"{M}x{N}x{K} c32={c32}")
 
 
-TILES = [(4104, 4104)]
+TILES = [(9, 4088), (60, 4088), (248, 4088), (504, 4088), (1016, 4088), (2040, 4080), (4104, 4104)]
 
 
 @pytest.mark.parametrize("c32", [0, 1])
-@pytest.mark.parametrize("M,N", TILES, ids=["256x256"])
+@pytest.mark.parametrize("M,N", TILES, ids=["16x16", "32x32", "64x64", "128x64", "128x128",
+                                            "256x128", "256x256"])
 def test_every_tile_at_its_edges(qf, M, N, c32):
     for K in (40, 64, 200, 576, 1096):
         _check(qf, M, N, K, c32)
