@@ -130,12 +130,24 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_small_kernel(NtArgs p) {
     __builtin_amdgcn_sched_barrier(0);
   };
   int buf = 0;                                   // buffer of group s
-  auto step = [&](int s, auto par) __attribute__((always_inline)) {
+  // FULL: groups s + 1 and s + NS - 1 exist and the latter is a whole one.  The main loop's steps
+  // are straight-line code: where the reads are conditional, the wait before the MFMAs is for the
+  // next group's reads too.
+  auto step = [&](int s, auto par, auto full) __attribute__((always_inline)) {
     constexpr int P = decltype(par)::value;
+    constexpr bool FULL = decltype(full)::value;
     const int nxt = buf == NS - 1 ? 0 : buf + 1, prev = buf == 0 ? NS - 1 : buf - 1;
-    if (s + 1 < n) {
-      wait_group(s + 1);
+    if (FULL) {
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 3) * U * NL));
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
       // every wavefront has multiplied group s - 1, so its buffer is free
+#pragma unroll
+      for (int u = 0; u < U; ++u) issue((s + NS - 1) * U + u, prev * U + u);
+      read_group(nxt, std::integral_constant<int, P ^ 1>{});
+      __builtin_amdgcn_sched_barrier(0);
+    } else if (s + 1 < n) {
+      wait_group(s + 1);
       if (s + NS - 1 < n) issue_group(s + NS - 1, prev);
       read_group(nxt, std::integral_constant<int, P ^ 1>{});
     }
@@ -150,7 +162,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_small_kernel(NtArgs p) {
             acc[i][j] = f32x4_t{};
           }
       }
-      if (s < n - 1 || x / 2 < last_u) mfma_slice(P, x);
+      if (FULL || s < n - 1 || x / 2 < last_u) mfma_slice(P, x);
     }
     __builtin_amdgcn_sched_barrier(0);
     buf = nxt;
@@ -160,9 +172,16 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_small_kernel(NtArgs p) {
     for (int s = 0; s < pre; ++s) issue_group(s, s);
     wait_group(0);
     read_group(0, std::integral_constant<int, 0>{});
-    for (int s = 0; s < n; s += 2) {
-      step(s, std::integral_constant<int, 0>{});
-      if (s + 1 < n) step(s + 1, std::integral_constant<int, 1>{});
+    const std::integral_constant<int, 0> even{};
+    const std::integral_constant<int, 1> odd{};
+    int s = 0;
+    for (; s + NS < n - 1; s += 2) {
+      step(s, even, std::true_type{});
+      step(s + 1, odd, std::true_type{});
+    }
+    for (; s < n; s += 2) {
+      step(s, even, std::false_type{});
+      if (s + 1 < n) step(s + 1, odd, std::false_type{});
     }
   }
   const int krem = (int)(K % BK);
