@@ -158,18 +158,22 @@ void saved_layout(const qf_qlinear_desc* d, void* saved, Packed* w, Packed* a) {
 // sets (an NT GEMM over 64 KB strides measured ~5 % slower than over 64 KB + 256 B; 16 KB
 // strides showed no difference), so those rows get 128 more elements.
 int64_t ws_ld(int64_t cols) { return cols % 16384 == 0 ? cols + 128 : cols; }
+// Columns of a transposed operand over M tokens: M rounded up to whole 16-byte groups (the ones past
+// M are written as zeros and contribute nothing to the contraction).
+int64_t pad8(int64_t M) { return (M + 7) / 8 * 8; }
+// The NT kernel addresses a tile's 256 rows with 32-bit byte offsets: row strides below this.
+constexpr int64_t kMaxNtRow = (int64_t)1 << 22;
 
 // Workspace of one linear layer (256-byte aligned regions):
 //   scal   256 B   weight amax scratch
 //   wpk    packed W_hat (when wfmt != NONE): the forward's GEMM operand (decoded inside the
 //                  GEMM), kept for a QF_FLAG_REUSE_WS backward when no saved buffer is given
 //   what   [N, K]  W_hat in bf16 (when wfmt != NONE): the operand of a materializing forward
-//                  and of the token-count-not-a-multiple-of-8 backward
 //   ahat   [M, K]  A_hat, when afmt != NONE
 //   whatt  [K, N]  W_hat^T (or W^T): right operand of dX = dY W_hat in NT form
 //   ahatt  [K, M]  A_hat^T (or X^T): right operand of dW = dY^T A_hat in NT form (row stride
-//                  ws_ld(M))
-//   dyt    [N, M]  dY^T: left operand of dW (row stride ws_ld(M))
+//                  ws_ld(pad8(M)))
+//   dyt    [N, M]  dY^T: left operand of dW (same row stride)
 //   part   FP32 partial tiles of the dW GEMM's split last round (qf::gemm_nt_split_bytes)
 struct LinearWs {
   float* scal;
@@ -187,7 +191,7 @@ size_t linear_ws_bytes(const qf_qlinear_desc* d) {
   size_t b = kAlign;
   if (d->wfmt != QF_FMT_NONE) b += packed_bytes(d->wfmt, d->N, d->K) + up(N * K * 2);
   if (d->afmt != QF_FMT_NONE) b += up(M * K * 2);
-  const size_t ldm = (size_t)ws_ld(d->M);
+  const size_t ldm = (size_t)ws_ld(pad8(d->M));
   b += up(K * N * 2) + up(K * ldm * 2) + up(N * ldm * 2);
   b += up(qf::gemm_nt_split_bytes(d->N, d->K));
   return b;
@@ -204,7 +208,7 @@ LinearWs linear_ws(const qf_qlinear_desc* d, void* ws) {
     w.what = reinterpret_cast<uint16_t*>(p); p += up(N * K * 2);
   }
   if (d->afmt != QF_FMT_NONE) { w.ahat = reinterpret_cast<uint16_t*>(p); p += up(M * K * 2); }
-  const size_t ldm = (size_t)ws_ld(d->M);
+  const size_t ldm = (size_t)ws_ld(pad8(d->M));
   w.whatt = reinterpret_cast<uint16_t*>(p); p += up(K * N * 2);
   w.ahatt = reinterpret_cast<uint16_t*>(p); p += up(K * ldm * 2);
   w.dyt = reinterpret_cast<uint16_t*>(p); p += up(N * ldm * 2);
@@ -565,64 +569,17 @@ qf_status qf_qlinear_bwd_ste(const qf_qlinear_desc* d, const uint16_t* dY, const
   // workspace's packed region; otherwise the operands are quantized again (identical bits).
   Packed sw{}, sa{};
   if (saved) saved_layout(d, const_cast<void*>(saved), &sw, &sa);
-  const Packed* src_w = saved ? &sw : (reuse ? &w.wpk : nullptr);
-  if (d->M % 8 == 0) {
-    // NT form: transposed operands through the workspace.  W_hat^T comes from the packed
-    // operand (transposing dequantizer) or straight from the transposing quantizer (one pass
-    // over W).  dY^T (left operand of dW) is written by the dX GEMM from the dY tiles it stages
-    // anyway when both gradients are asked for; otherwise by the transpose kernel.
-    const int64_t ldm = ws_ld(d->M);
-    const bool dyt_by_dx = dX != nullptr && dW != nullptr && ldm < qf::kGemmAtMaxLd;
-    if (dX) {  // dX[M, K] = dY[M, N] (W_hat^T)[K, N]^T
-      if (d->wfmt != QF_FMT_NONE) {
-        if (src_w) {
-          QF_TRY(dev(qf::launch_dequant_t(d->wfmt, src_w->codes, src_w->scales, src_w->S, d->N,
-                                          d->K, w.whatt, d->N, s), "dequantize W (transposed)"));
-        } else {
-          const float* g = d->w_amax;
-          if (d->wfmt == QF_FMT_NVFP4 && !g) {
-            QF_TRY(dev(qf::launch_amax(W, d->N, d->K, dm.ldw, w.scal, false, s), "amax"));
-            g = w.scal;
-          }
-          QF_TRY(dev(qf::launch_quant_t(d->wfmt, W, d->N, d->K, dm.ldw, 1, 0, g, w.whatt, d->N, 0,
-                                        s), "quantize W (transposed)"));
-        }
-      } else {
-        QF_TRY(dev(qf::launch_transpose_bf16(W, d->N, d->K, dm.ldw, w.whatt, d->N, 1, 0, 0, s),
-                   "transpose W"));
-      }
-      QF_TRY(dev(qf::launch_gemm_nt(d->M, d->K, d->N, dY, dm.ldy, 0, w.whatt, d->N, 0, dX,
-                                    dm.ldx, 0, nullptr, s, dyt_by_dx ? w.dyt : nullptr, ldm),
-                 "dX gemm"));
-    }
-    if (dW) {  // dW[N, K] = (dY^T)[N, M] (A_hat^T)[K, M]^T
-      if (!dyt_by_dx)
-        QF_TRY(dev(qf::launch_transpose_bf16(dY, d->M, d->N, dm.ldy, w.dyt, ldm, 1, 0, 0, s),
-                   "transpose dY"));
-      if (forward_writes_at(d)) {
-        // A_hat^T is in the workspace already: the forward's GEMM wrote it
-      } else if (d->afmt != QF_FMT_NONE && saved) {
-        QF_TRY(dev(qf::launch_dequant_t(d->afmt, sa.codes, sa.scales, sa.S, d->M, d->K, w.ahatt,
-                                        ldm, s), "dequantize X (transposed)"));
-      } else if (d->afmt != QF_FMT_NONE && !reuse) {
-        QF_TRY(dev(qf::launch_quant_t(d->afmt, X, d->M, d->K, dm.ldx, 1, 0, d->a_amax, w.ahatt,
-                                      ldm, 0, s), "quantize X (transposed)"));
-      } else {
-        const uint16_t* src = d->afmt != QF_FMT_NONE ? w.ahat : X;
-        const int64_t ld = d->afmt != QF_FMT_NONE ? d->K : dm.ldx;
-        QF_TRY(dev(qf::launch_transpose_bf16(src, d->M, d->K, ld, w.ahatt, ldm, 1, 0, 0, s),
-                   "transpose A_hat"));
-      }
-      QF_TRY(dev(qf::launch_gemm_nt(d->N, d->K, d->M, w.dyt, ldm, 0, w.ahatt, ldm, 0, dW, d->K,
-                                    1, w.part, s),
-                 "dW gemm"));
-    }
-  } else {
-    // Token count not a multiple of 8 (no 16-byte transposed rows): the NT kernel reads
-    // W_hat [N, K], dY [M, N] and A_hat [M, K] in place as operands stored [K'][*], through
-    // transposing LDS reads (slower than the transposed operands, correct for any M).  W_hat is
-    // quantized again into the workspace (the forward may have left only its packed form);
-    // A_hat is the forward's with QF_FLAG_REUSE_WS.
+  const Packed* src_w = saved ? &sw : (reuse && d->M % 8 == 0 ? &w.wpk : nullptr);
+  // NT form: transposed operands through the workspace.  W_hat^T comes from the packed
+  // operand (transposing dequantizer) or straight from the transposing quantizer (one pass
+  // over W).  dY^T (left operand of dW) is written by the dX GEMM from the dY tiles it stages
+  // anyway when both gradients are asked for; otherwise by the transpose kernel.
+  const int64_t Mp = pad8(d->M), ldm = ws_ld(Mp);
+  if (d->M % 8 != 0 && ldm >= kMaxNtRow) {
+    // A ragged token count whose transposed rows are too long for the NT kernel's 32-bit offsets
+    // within a tile: the products read W_hat [N, K], dY [M, N] and A_hat [M, K] in place, as
+    // operands stored [K'][*], through transposing LDS reads (about twice the time).  W_hat is
+    // quantized again into the workspace; A_hat is the forward's with QF_FLAG_REUSE_WS.
     const uint16_t *Wop, *Aop;
     int64_t ldw_op, lda_op;
     QF_TRY(quantize_operands(d, dm, X, W, w, dX != nullptr, !reuse && dW != nullptr,
@@ -635,6 +592,52 @@ qf_status qf_qlinear_bwd_ste(const qf_qlinear_desc* d, const uint16_t* dY, const
       QF_TRY(dev(qf::launch_gemm_nt(d->N, d->K, d->M, dY, dm.ldy, 1, Aop, lda_op, 1, dW, d->K, 1,
                                     w.part, s),
                  "dW gemm"));
+    return ok();
+  }
+  const bool dyt_by_dx = dX != nullptr && dW != nullptr && ldm < qf::kGemmAtMaxLd;
+  if (dX) {  // dX[M, K] = dY[M, N] (W_hat^T)[K, N]^T
+    if (d->wfmt != QF_FMT_NONE) {
+      if (src_w) {
+        QF_TRY(dev(qf::launch_dequant_t(d->wfmt, src_w->codes, src_w->scales, src_w->S, d->N,
+                                        d->K, w.whatt, d->N, s), "dequantize W (transposed)"));
+      } else {
+        const float* g = d->w_amax;
+        if (d->wfmt == QF_FMT_NVFP4 && !g) {
+          QF_TRY(dev(qf::launch_amax(W, d->N, d->K, dm.ldw, w.scal, false, s), "amax"));
+          g = w.scal;
+        }
+        QF_TRY(dev(qf::launch_quant_t(d->wfmt, W, d->N, d->K, dm.ldw, 1, 0, g, w.whatt, d->N, 0,
+                                      s), "quantize W (transposed)"));
+      }
+    } else {
+      QF_TRY(dev(qf::launch_transpose_bf16(W, d->N, d->K, dm.ldw, w.whatt, d->N, 1, 0, 0, s),
+                 "transpose W"));
+    }
+    QF_TRY(dev(qf::launch_gemm_nt(d->M, d->K, d->N, dY, dm.ldy, 0, w.whatt, d->N, 0, dX,
+                                  dm.ldx, 0, nullptr, s, dyt_by_dx ? w.dyt : nullptr, ldm),
+               "dX gemm"));
+  }
+  if (dW) {  // dW[N, K] = (dY^T)[N, M] (A_hat^T)[K, M]^T
+    if (!dyt_by_dx)
+      QF_TRY(dev(qf::launch_transpose_bf16(dY, d->M, d->N, dm.ldy, w.dyt, ldm, 1, 0, 0, s),
+                 "transpose dY"));
+    if (forward_writes_at(d)) {
+      // A_hat^T is in the workspace already: the forward's GEMM wrote it
+    } else if (d->afmt != QF_FMT_NONE && saved) {
+      QF_TRY(dev(qf::launch_dequant_t(d->afmt, sa.codes, sa.scales, sa.S, d->M, d->K, w.ahatt,
+                                      ldm, s), "dequantize X (transposed)"));
+    } else if (d->afmt != QF_FMT_NONE && !reuse) {
+      QF_TRY(dev(qf::launch_quant_t(d->afmt, X, d->M, d->K, dm.ldx, 1, 0, d->a_amax, w.ahatt,
+                                    ldm, 0, s), "quantize X (transposed)"));
+    } else {
+      const uint16_t* src = d->afmt != QF_FMT_NONE ? w.ahat : X;
+      const int64_t ld = d->afmt != QF_FMT_NONE ? d->K : dm.ldx;
+      QF_TRY(dev(qf::launch_transpose_bf16(src, d->M, d->K, ld, w.ahatt, ldm, 1, 0, 0, s),
+                 "transpose A_hat"));
+    }
+    QF_TRY(dev(qf::launch_gemm_nt(d->N, d->K, Mp, w.dyt, ldm, 0, w.ahatt, ldm, 0, dW, d->K,
+                                  1, w.part, s),
+               "dW gemm"));
   }
   return ok();
 }

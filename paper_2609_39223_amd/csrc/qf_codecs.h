@@ -765,7 +765,8 @@ __device__ __forceinline__ uint4 block_row_transposed(const uint32_t w[8][4], in
 }
 
 // out[c0 + k][oc0 + r] = tile(r, k) for the 64 x 256 tile in LDS (after a barrier); output rows
-// at or past K and output columns at or past col_end are skipped (both multiples of 8).
+// at or past K (a multiple of 8) are skipped, as are groups of eight output columns that start
+// at or past col_end.
 __device__ __forceinline__ void store_tile_transposed(const uint4* tile, int t, uint16_t* out,
                                                       int64_t ldo, int64_t c0, int64_t oc0,
                                                       int64_t K, int64_t col_end) {

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
     tile_origin<BM, BN>(p, t, m0, n0);
     m_end = p.M;
     at_col0 = m0;
-    at_end = m_end;
+    at_end = (m_end + 7) / 8 * 8;                // (rows past the last of a ragged M: zeros)
   } else {
     // The grid is sized for the most row tiles any routing can need; the real count is
     // tile_start[E].  Block b runs on XCD x = b % 8 as its item j = b / 8, and XCD x takes the
@@ -536,10 +536,12 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
   // byte offset of this lane's 8 bytes of piece 0 within a stage's rows of A^T (below 2^31)
   const int at_off = (int)(((int64_t)at_c * p.ldat + at_col0 + at_r) * 2);
   const int at_ld8 = (int)(p.ldat * 8);          // bytes of 4 rows of A^T
-  const bool at_rok = m0 + at_r < m_end;          // data rows
+  // data rows of the four, as masks of the packed values
+  const uint32_t at_m01 = (m0 + at_r < m_end ? 0xFFFFu : 0u) | (m0 + at_r + 1 < m_end ? 0xFFFF0000u : 0u);
+  const uint32_t at_m23 = (m0 + at_r + 2 < m_end ? 0xFFFFu : 0u) | (m0 + at_r + 3 < m_end ? 0xFFFF0000u : 0u);
   const bool at_zok = at_col0 + at_r < at_end;     // data or zero-padding columns
   auto at_store = [&](int64_t se, int kvalid, int u, u32x4_t h) __attribute__((always_inline)) {
-    const u32x2_t v = at_rok ? u32x2_t{h[0] | (h[1] << 16), h[2] | (h[3] << 16)} : u32x2_t{0, 0};
+    const u32x2_t v = {(h[0] | (h[1] << 16)) & at_m01, (h[2] | (h[3] << 16)) & at_m23};
     const bool ok = at_zok && 4 * u + at_c < kvalid;
     const int off = ok ? at_off + u * at_ld8 : 0x7FFFFFF8;
     __builtin_amdgcn_raw_buffer_store_b64(
@@ -579,7 +581,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
   // bytes of a stage's rows of A^T (below 2^31: ldat < 2^24)
   const uint32_t at_sbytes = (uint32_t)(BK * p.ldat * 2);
   auto at_pack = [&](const u32x4_t& h) __attribute__((always_inline)) -> u32x2_t {
-    return at_rok ? u32x2_t{h[0] | (h[1] << 16), h[2] | (h[3] << 16)} : u32x2_t{0, 0};
+    return u32x2_t{(h[0] | (h[1] << 16)) & at_m01, (h[2] | (h[3] << 16)) & at_m23};
   };
   auto at_put = [&](__amdgpu_buffer_rsrc_t r, int u, u32x2_t v) __attribute__((always_inline)) {
     const int off = at_zok && u < 16 ? at_off + u * at_ld8 : 0x7FFFFFF8;
@@ -976,7 +978,7 @@ hipError_t launch_dense(int64_t M, int64_t N, int64_t K, const uint16_t* A, int6
                         const uint16_t* B, int64_t ldb, int b_mn, bool bf, void* C, int64_t ldc,
                         int c_f32, float* part, hipStream_t s, uint16_t* at, int64_t ldat) {
   // (a stage's 64 rows of A^T, 128 ldat bytes, stay below 2^31: 32-bit store offsets)
-  if (at != nullptr && (c_f32 || a_mn || b_mn || M % 8 != 0 || ldat < M || ldat % 4 != 0 ||
+  if (at != nullptr && (c_f32 || a_mn || b_mn || ldat < (M + 7) / 8 * 8 || ldat % 4 != 0 ||
                         ldat >= kGemmAtMaxLd || reinterpret_cast<uintptr_t>(at) % 8 != 0))
     return hipErrorInvalidValue;
   if (bf && (a_mn || b_mn || K % BK != 0 || reinterpret_cast<uintptr_t>(B) % 16 != 0))

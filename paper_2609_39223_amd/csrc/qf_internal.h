@@ -39,7 +39,8 @@ hipError_t launch_nvfp4_batched(const uint16_t* x, int64_t E, int64_t R, int64_t
 
 // Quantize-dequantize with transposed output: out[k][r] = x_hat[r][k] (bf16, row stride ldo)
 // for `batch` tensors spaced xbs / obs elements apart (NVFP4: tensor amax g[z] per tensor).
-// R and K multiples of 8, K a multiple of the format block.
+// K a multiple of 8 and of the format block; a ragged R (batch 1) also writes zeros up to the next
+// multiple of 8.
 hipError_t launch_quant_t(int fmt, const uint16_t* x, int64_t R, int64_t K, int64_t ldx,
                           int64_t batch, int64_t xbs, const float* g, uint16_t* out, int64_t ldo,
                           int64_t obs, hipStream_t s);
@@ -47,7 +48,8 @@ hipError_t launch_quant_t(int fmt, const uint16_t* x, int64_t R, int64_t K, int6
 // stride ldo) of a [R, K] tensor stored as codes [R][K/2] + scales [R][K/16 | K/32] (NVFP4
 // with its tensor decode scale S = g / 2688 at S) or Q4_K blocks [R][K/256][144] (in
 // `codes`); bit-identical to launch_quant_t's x_hat of the tensor those codes came from.
-// R and K multiples of 8 (Q4K: K of 256).
+// K a multiple of 8 (Q4K: of 256); a ragged R (batch 1) also writes zeros up to the next
+// multiple of 8.
 // batch > 1: that many [R, K] tensors stored back to back (decode scale S[z]), tensor z's
 // output obs elements after tensor z - 1's.
 hipError_t launch_dequant_t(int fmt, const uint8_t* codes, const uint8_t* scales,
@@ -63,9 +65,9 @@ hipError_t launch_quant_t_grouped(int fmt, const uint16_t* x, int64_t T, int64_t
 // ---- GEMMs --------------------------------------------------------------------------------
 // NT GEMM (qf_gemm_nt.hip): C[m, n] = sum_k A(m, k) B(n, k).  A is [M][K] (k contiguous) or,
 // with a_mn, [K][M] (m contiguous); likewise B [N][K] or [K][N] with b_mn.  Row strides and
-// K multiples of 8.  With `at` (bf16 C, both operands k-major, M % 8 == 0, M <= ldat <
-// kGemmAtMaxLd, ldat a multiple of 4, at 8-byte aligned) the launch also writes A^T [K][M]
-// (row stride ldat): from the tiles it stages anyway when N spans at least 8 tile columns,
+// K multiples of 8.  With `at` (bf16 C, both operands k-major, M rounded up to a multiple of 8
+// <= ldat < kGemmAtMaxLd, ldat a multiple of 4, at 8-byte aligned) the launch also writes A^T
+// [K][M] (row stride ldat, zeros in columns M up to the next multiple of 8): from the tiles it stages anyway when N spans at least 8 tile columns,
 // else with the transpose kernel; other arguments give hipErrorInvalidValue.
 constexpr int64_t kGemmAtMaxLd = (int64_t)1 << 24;
 hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const uint16_t* A, int64_t lda,
@@ -112,7 +114,7 @@ hipError_t launch_grouped_nt_rows(int64_t E, int64_t T, int64_t N, int64_t K, co
                                   uint16_t* at = nullptr, int64_t ldat = 0,
                                   const int* kstart = nullptr);
 // bf16 transpose (qf_transpose.hip): out[c][r] = in[r][c] for `batch` matrices spaced ibs / obs
-// elements apart; R and C multiples of 8.
+// elements apart; C a multiple of 8; a ragged R also writes zeros up to the next multiple of 8.
 hipError_t launch_transpose_bf16(const uint16_t* in, int64_t R, int64_t C, int64_t ldi,
                                  uint16_t* out, int64_t ldo, int64_t batch, int64_t ibs,
                                  int64_t obs, hipStream_t s);

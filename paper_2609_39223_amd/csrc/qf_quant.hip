@@ -459,7 +459,8 @@ __global__ __launch_bounds__(kThreads) void quant_t_kernel(const uint16_t* __res
 #pragma unroll
       for (int k = 0; k < 8; ++k) xh[k] = h[k];
     }
-    tile[row * 32 + tslot(row, cc)] = pack8(xh);
+    // (rows past the last are zeros whatever the tensor scale)
+    tile[row * 32 + tslot(row, cc)] = r0 + row < r_end ? pack8(xh) : make_uint4(0, 0, 0, 0);
   }
   __syncthreads();
   store_tile_transposed(tile, t, out, ldo, c0, oc0, K, GROUPED ? INT64_MAX : R);
@@ -542,7 +543,9 @@ __global__ __launch_bounds__(kThreads) void dequant_t_kernel(const uint8_t* __re
       const uint32_t qw[2] = {cw[i], sc[i]};
       q4k_decode8(qw, t1, t2, w);
     }
-    tile[row * 32 + tslot(row, cc)] = make_uint4(w[0], w[1], w[2], w[3]);
+    // (rows past the last are zeros whatever the tensor scale)
+    tile[row * 32 + tslot(row, cc)] = r0 + row < R ? make_uint4(w[0], w[1], w[2], w[3])
+                                                   : make_uint4(0, 0, 0, 0);
   }
   __syncthreads();
   store_tile_transposed(tile, t, out, ldo, c0, r0, K, R);

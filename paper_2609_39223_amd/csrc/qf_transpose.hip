@@ -10,7 +10,8 @@
 // 47-58 us at 14336 x 4096 against 47.5 us for this form, which needs no barrier.  (The grouped
 // transposes of the expert layer keep the LDS tile of the transposing quantizer: this form
 // measured 625 against 600 us there.)
-// R and C must be multiples of 8 (16-byte chunks).
+// C must be a multiple of 8 (16-byte chunks); columns past a ragged R up to the next multiple of 8
+// are written as zeros.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
