@@ -1526,33 +1526,23 @@ qf_status qf_export_fused(int fmt, const qf_member* members, int n, int64_t K, u
   if (fmt == QF_FMT_NVFP4) {
     if (!w_amax) return fail(QF_EINVAL, "%s: NVFP4 needs w_amax", fn);
     if (input_scale && !a_amax) return fail(QF_EINVAL, "%s: input_scale needs a_amax", fn);
-    for (int i = 0; i < n; ++i)       // the first member sets g, the others fold into it
-      QF_TRY(dev(qf::launch_amax(members[i].W, members[i].rows, K, members[i].ldw, w_amax,
-                                 i > 0, s),
-                 "tied amax"));
-    int64_t r0 = 0;
-    for (int i = 0; i < n; ++i) {
-      QF_TRY(dev(qf::launch_nvfp4(members[i].W, members[i].rows, K, members[i].ldw, w_amax,
-                                  nullptr, codes + r0 * (K / 2), scales + r0 * (K / 16), nullptr,
-                                  s),
-                 "nvfp4 member"));
-      r0 += members[i].rows;
-    }
-    if (weight_scale_2 || input_scale)
-      QF_TRY(dev(qf::launch_export_scalars(w_amax, a_amax, weight_scale_2, input_scale, s),
-                 "export scalars"));
-  } else {
-    if (w_amax || weight_scale_2 || input_scale)
-      return fail(QF_EINVAL, "%s: MXFP4 has no tensor-level scales", fn);
-    int64_t r0 = 0;
-    for (int i = 0; i < n; ++i) {
-      QF_TRY(dev(qf::launch_mxfp4(members[i].W, members[i].rows, K, members[i].ldw,
-                                  codes + r0 * (K / 2), scales + r0 * (K / 32), nullptr, s),
-                 "mxfp4 member"));
-      r0 += members[i].rows;
-    }
+  } else if (w_amax || weight_scale_2 || input_scale) {
+    return fail(QF_EINVAL, "%s: MXFP4 has no tensor-level scales", fn);
   }
-  (void)N;
+  if (N == 0 || K == 0) {             // no elements: amax and weight_scale_2 are zero
+    if (fmt == QF_FMT_NVFP4) {
+      QF_TRY(dev(qf::launch_fill_f32(w_amax, 1, 0.0f, s), "tied amax"));
+      if (weight_scale_2 || input_scale)
+        QF_TRY(dev(qf::launch_export_scalars(w_amax, a_amax, weight_scale_2, input_scale, s),
+                   "export scalars"));
+    }
+    return ok();
+  }
+  qf::ExportMember m[8];
+  for (int i = 0; i < n; ++i) m[i] = {members[i].W, members[i].rows, members[i].ldw};
+  QF_TRY(dev(qf::launch_export_members(fmt, m, n, K, codes, scales, w_amax, weight_scale_2, a_amax,
+                                       input_scale, s),
+             "export"));
   return ok();
 }
 

@@ -20,6 +20,16 @@ hipError_t launch_amax(const uint16_t* x, int64_t R, int64_t K, int64_t ldx, flo
 hipError_t launch_nvfp4(const uint16_t* x, int64_t R, int64_t K, int64_t ldx, const float* g,
                         float* s_out, uint8_t* codes, uint8_t* scales, uint16_t* xhat,
                         hipStream_t s, bool stream_out = false);
+// The row concatenation of up to eight members (rows x K, row strides ldw; some rows and K > 0):
+// NVFP4 codes, scales, tied amax, S = amax / 2688 (ws2, may be null) and input_scale = *a_amax / 2688
+// (may be null), or MXFP4 codes and scales.
+struct ExportMember {
+  const uint16_t* W;
+  int64_t rows, ldw;
+};
+hipError_t launch_export_members(int fmt, const ExportMember* members, int n, int64_t K,
+                                 uint8_t* codes, uint8_t* scales, float* w_amax, float* ws2,
+                                 const float* a_amax, float* input_scale, hipStream_t s);
 hipError_t launch_mxfp4(const uint16_t* x, int64_t R, int64_t K, int64_t ldx, uint8_t* codes,
                         uint8_t* scales, uint16_t* xhat, hipStream_t s);
 hipError_t launch_q4k(const uint16_t* x, int64_t R, int64_t K, int64_t ldx, uint8_t* packed,

@@ -106,3 +106,51 @@ def test_weight_sync_payload(qf, fmt):
         assert p["scalars"][1] == np.float32(ref["input_scale"])
     else:
         assert list(p["scalars"]) == [0.0, 0.0]
+
+
+@pytest.mark.parametrize("rows,pads,K", [((1, 3, 7), (0, 0, 0), 1024), ((64, 5, 2, 33), (0, 8, 0, 64), 272),
+                                         ((130, 1), (0, 0), 2080), ((600,), (0,), 4096),
+                                         ((17,) * 8, (0,) * 8, 64)])
+@pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4"])
+def test_fused_export_equals_member_by_member(qf, fmt, rows, pads, K):
+    """One pass over the concatenated rows (odd and single rows, strided members, up to eight) against the quantizer of each member with the tied amax: the same bytes."""
+    if fmt == "mxfp4":
+        K = K // 32 * 32
+    rng = np.random.default_rng(sum(rows) + K)
+    mem = []
+    for i, (r, p) in enumerate(zip(rows, pads)):
+        buf = np.full((r, K + p), 0x7FC0, np.uint16)        # NaN padding: never read
+        buf[:, :K] = workloads.normal_bf16(rng, (r, K), 0.02 * (i + 1))
+        mem.append(to_dev(buf)[:, :K])
+    N, B = sum(rows), 16 if fmt == "nvfp4" else 32
+    u8 = dict(dtype=torch.uint8, device="cuda")
+    codes, scales = torch.full((N, K // 2), 9, **u8), torch.full((N, K // B), 9, **u8)
+    codes2, scales2 = torch.full((N, K // 2), 5, **u8), torch.full((N, K // B), 5, **u8)
+    f = [torch.full((1,), -1.0, device="cuda") for _ in range(4)]
+    run = torch.full((1,), 3.5, device="cuda")
+    if fmt == "nvfp4":
+        qf.export_fused(mem, fmt, codes, scales, w_amax=f[0], weight_scale_2=f[1], a_amax=run,
+                        input_scale=f[2])
+    else:
+        qf.export_fused(mem, fmt, codes, scales)
+    for i, m in enumerate(mem):
+        if fmt == "nvfp4":
+            qf.amax(m, f[3], accumulate=i > 0)
+    r0 = 0
+    for m in mem:
+        r1 = r0 + m.shape[0]
+        if r1 > r0 and fmt == "nvfp4":
+            c, sc = torch.empty(r1 - r0, K // 2, **u8), torch.empty(r1 - r0, K // B, **u8)
+            qf.fakequant_nvfp4(m, f[3], qf.AMAX_GIVEN, None, c, sc, None)
+            codes2[r0:r1], scales2[r0:r1] = c, sc
+        elif r1 > r0:
+            c, sc = torch.empty(r1 - r0, K // 2, **u8), torch.empty(r1 - r0, K // B, **u8)
+            qf.fakequant_mxfp4(m, c, sc, None)
+            codes2[r0:r1], scales2[r0:r1] = c, sc
+        r0 = r1
+    torch.cuda.synchronize()
+    assert torch.equal(codes, codes2) and torch.equal(scales, scales2)
+    if fmt == "nvfp4":
+        assert f[0].item() == f[3].item()
+        assert f[1].item() == float(np.float32(f[0].item()) / np.float32(2688.0))
+        assert f[2].item() == float(np.float32(3.5) / np.float32(2688.0))
