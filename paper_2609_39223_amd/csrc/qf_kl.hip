@@ -2,24 +2,32 @@
 // teacher and student logits (bf16 [L, V]), the forward KL of the two softmax distributions,
 // its gradient with respect to the student's logits, and the teacher-student top-1 agreement.
 //
-// One workgroup per row, two passes over the row:
-//   pass 1  online base-2 statistics of both rows, with a = z log2(e):
-//             m = max a,  S = sum 2^(a - m)                         (teacher and student)
+// Two passes over a row, with a = z log2(e):
+//   pass 1  base-2 statistics of both rows around a reference m,
+//             S = sum 2^(a - m)                                      (teacher and student)
 //             Q = sum 2^(a_T - m_T) (z_T - z_S)                      (teacher-weighted gap)
-//           and the first index of each row's maximum logit.  Each 8-logit chunk updates the
-//           maxima from its raw maximum (z -> z log2(e) is monotone), each exponent is one
-//           FMA (z log2(e) - m), and the index search runs only when a chunk's maximum beats
-//           the lane's running one.  Then, in natural units,
+//           and the first chunk that holds each row's maximum logit.  Then, in natural units,
 //             lse = ln2 (m + log2 S),   KL = Q / S_T + lse_S - lse_T
 //           (sum_v p_T (log p_T - log p_S) with log p = z - lse).
 //   pass 2  grad[v] = scale (2^(a_S - c_S) - 2^(a_T - c_T)), c = m + log2 S, i.e.
 //           scale (p_S - p_T), written as bf16.
-// Each lane folds its 16-byte chunks in a fixed order and the workgroup merges the lanes'
-// statistics in a fixed tree, so the results are deterministic.  One 1024-lane workgroup
-// fits a CU (68 VGPRs: 7 waves per SIMD), so 256 rows (~155 MB of logits at a 152K
-// vocabulary) are in flight, and part of the second read hits the 256 MB last-level cache;
-// the gradient goes out with non-temporal stores so it does not evict the logits (512-lane
-// workgroups, two per CU, read faster in the first pass but lose that reuse: slower overall).
+// What bounds it is HBM (6 bytes per logit) and, nearly as much, the vector units: four exponents,
+// at a quarter of the rate, and about 20 other operations per logit.  So
+//  - a row is read once: of the 16 waves' chunks a compute unit keeps 8 pairs per lane in registers
+//    and 4 in LDS (384 KB of the 594 KB of a 151936-logit row pair); only the rest is read again,
+//    mostly from L2 and the last-level cache.
+//  - a workgroup stays on its unit and walks over rows; a register pair is refilled from the next
+//    row as soon as its gradient is out, so loads run on through pass 2 and the row change.  Narrow
+//    vocabularies take two 512-lane workgroups a unit, whose passes overlap.
+//  - the reference of a lane's sums moves only when a chunk's maximum passes it by 2^16 (exact up
+//    to rounding, as the sums are in floating point), so few chunks rescale; the element of a
+//    maximum is looked for once a row, and only where both maxima are in one chunk.
+// 4096 x 151936: 945 -> 784 us; 8192 x 32000: 444 -> 321; 2048 x 65536: 221 -> 169 (against one
+// workgroup per row reading it twice; keeping alone 880 / 456 / 210, with the refills 830 / 345 /
+// 193).  Each lane folds its 16-byte chunks in a fixed order and the workgroup merges the lanes'
+// statistics in a fixed tree, so the results are deterministic.  The gradient goes out with
+// non-temporal stores so it does not evict the logits; a lane reads its chunks for the last time
+// before it writes their gradient.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -34,10 +42,13 @@ using namespace codec;
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr int kUnroll = 2;                            // chunks per lane in flight per operand
+constexpr int kCUs = 256;                             // compute units
+constexpr float kSlack = 16.0f;                       // how far a maximum may pass the reference
+constexpr int kNt = 2;                                // buffer operation: non-temporal
+constexpr int kKeepLds = 4, kKeepReg = 8;             // chunk pairs a lane keeps for the gradient
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-struct Stat {   // online softmax statistics in base 2
+struct Stat {   // softmax statistics in base 2 around the reference m
   float m, S, Q;
 };
 
@@ -45,7 +56,7 @@ __device__ __forceinline__ float exp2_safe(float d) {   // 2^d with 2^(-inf) = 0
   return __builtin_amdgcn_exp2f(d);
 }
 
-// (m1, S1, Q1) + (m2, S2, Q2) -> common maximum; an empty side (m = -inf) contributes nothing.
+// (m1, S1, Q1) + (m2, S2, Q2) -> the larger reference; an empty side (m = -inf) contributes nothing.
 __device__ __forceinline__ Stat merge(Stat x, Stat y) {
   const float m = fmaxf(x.m, y.m);
   const float fx = x.m == m ? 1.0f : exp2_safe(x.m - m);
@@ -53,9 +64,19 @@ __device__ __forceinline__ Stat merge(Stat x, Stat y) {
   return Stat{m, x.S * fx + y.S * fy, x.Q * fx + y.Q * fy};
 }
 
-struct ArgMax {  // value and first index of a maximum
+struct ArgMax {  // value of a maximum and the first chunk that holds it
   float v;
   int64_t i;
+};
+
+struct LaneMax {  // the same within a lane: the number of its chunk
+  float v;
+  uint32_t i;
+};
+
+struct WaveStat {
+  Stat st, ss;
+  ArgMax at, as;
 };
 
 __device__ __forceinline__ ArgMax amax_merge(ArgMax x, ArgMax y) {
@@ -73,9 +94,15 @@ __device__ __forceinline__ void unpack8_f32(uint4 v, float x[8]) {
   }
 }
 
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float m;   // fmaxf would first quiet signalling NaNs, one instruction an operand
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+  return m;
+}
+
 __device__ __forceinline__ float max8(const float x[8]) {
-  return fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])),
-               fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+  const float a = max3(x[0], x[1], x[2]), b = max3(x[3], x[4], x[5]);
+  return max3(max3(a, x[6], x[7]), b, b);
 }
 
 // First k with x[k] == m (m is the maximum of x, so one exists).
@@ -86,145 +113,246 @@ __device__ __forceinline__ int first_eq8(const float x[8], float m) {
   return k0;
 }
 
-template <int NT>
-__global__ __launch_bounds__(NT) void qad_kl_kernel(const uint16_t* __restrict__ zt, int64_t ldt,
-                                                    const uint16_t* __restrict__ zs, int64_t lds_,
-                                                    int64_t V, float gscale,
-                                                    float* __restrict__ row_kl,
-                                                    uint16_t* __restrict__ grad, int64_t ldg,
-                                                    int32_t* __restrict__ agree) {
-  constexpr int NW = NT / 64;
-  __shared__ float sm_t[NW], sS_t[NW], sQ[NW], sm_s[NW], sS_s[NW];
-  __shared__ float sva[NW], svb[NW];
-  __shared__ int64_t sia[NW], sib[NW];
-  __shared__ float row_c[2];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int64_t row = blockIdx.x;
-  const uint16_t* pt = zt + row * ldt;
-  const uint16_t* ps = zs + row * lds_;
-  const int64_t chunks = V >> 3;
-
-  Stat st{-__builtin_huge_valf(), 0.0f, 0.0f};
-  Stat ss{-__builtin_huge_valf(), 0.0f, 0.0f};
-  ArgMax at{-__builtin_huge_valf(), INT64_MAX}, as{-__builtin_huge_valf(), INT64_MAX};
-
-  for (int64_t c0 = t; c0 < chunks; c0 += (int64_t)NT * kUnroll) {
-    uint4 vt[kUnroll], vs[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {               // all loads first
-      const int64_t c = c0 + (int64_t)u * NT;
-      vt[u] = make_uint4(0, 0, 0, 0);
-      vs[u] = make_uint4(0, 0, 0, 0);
-      if (c < chunks) {
-        vt[u] = *reinterpret_cast<const uint4*>(pt + c * 8);
-        vs[u] = *reinterpret_cast<const uint4*>(ps + c * 8);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int64_t c = c0 + (int64_t)u * NT;
-      if (c >= chunks) break;
-      float xt[8], xs[8];
-      unpack8_f32(vt[u], xt);
-      unpack8_f32(vs[u], xs);
-      const float mt = max8(xt), ms = max8(xs);
-      if (mt > at.v) at = ArgMax{mt, c * 8 + first_eq8(xt, mt)};
-      if (ms > as.v) as = ArgMax{ms, c * 8 + first_eq8(xs, ms)};
-      // rescale the running sums to the new maxima, then add the chunk
-      const float nmt = fmaxf(st.m, mt * kLog2e), nms = fmaxf(ss.m, ms * kLog2e);
-      const float ft = st.m == nmt ? 1.0f : exp2_safe(st.m - nmt);
-      const float fs = ss.m == nms ? 1.0f : exp2_safe(ss.m - nms);
-      float S_t = st.S * ft, Q_t = st.Q * ft, S_s = ss.S * fs;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float et = exp2_safe(__builtin_fmaf(xt[k], kLog2e, -nmt));
-        S_t += et;
-        Q_t = __builtin_fmaf(et, xt[k] - xs[k], Q_t);
-        S_s += exp2_safe(__builtin_fmaf(xs[k], kLog2e, -nms));
-      }
-      st = Stat{nmt, S_t, Q_t};
-      ss = Stat{nms, S_s, 0.0f};
-    }
+// Folds a lane's 8-logit chunk number i into its statistics.
+__device__ __forceinline__ void fold_chunk(uint4 vt, uint4 vs, uint32_t i, Stat& st, Stat& ss,
+                                           LaneMax& at, LaneMax& as) {
+  float xt[8], xs[8];
+  unpack8_f32(vt, xt);
+  unpack8_f32(vs, xs);
+  const float mt = max8(xt), ms = max8(xs);
+  if (mt > at.v) at = LaneMax{mt, i};
+  if (ms > as.v) as = LaneMax{ms, i};
+  const float nmt = mt * kLog2e, nms = ms * kLog2e;
+  if (nmt > st.m + kSlack || nms > ss.m + kSlack) {   // new references
+    const float rt = fmaxf(st.m, nmt), rs = fmaxf(ss.m, nms);
+    const float ft = st.m == rt ? 1.0f : exp2_safe(st.m - rt);
+    const float fs = ss.m == rs ? 1.0f : exp2_safe(ss.m - rs);
+    st = Stat{rt, st.S * ft, st.Q * ft};
+    ss = Stat{rs, ss.S * fs, 0.0f};
   }
-
-  // workgroup merge in a fixed tree: within each wave by halving offsets, then waves in order
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
+  for (int k = 0; k < 8; ++k) {
+    const float et = exp2_safe(__builtin_fmaf(xt[k], kLog2e, -st.m));
+    st.S += et;
+    st.Q = __builtin_fmaf(et, xt[k] - xs[k], st.Q);
+    ss.S += exp2_safe(__builtin_fmaf(xs[k], kLog2e, -ss.m));
+  }
+}
+
+// The gradient of one chunk.  Finite row statistics make every probability finite, so the
+// hardware bf16 pack rounds exactly as bf16_rne; rows with non-finite logits keep the bit-level
+// rounding (uniform per workgroup).
+__device__ __forceinline__ void grad_chunk(uint4 vt, uint4 vs, float ct, float cs, float gscale,
+                                           bool finite, __amdgpu_buffer_rsrc_t out, uint32_t off) {
+  float xt[8], xs[8], g[8];
+  unpack8_f32(vt, xt);
+  unpack8_f32(vs, xs);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const float p_t = exp2_safe(__builtin_fmaf(xt[k], kLog2e, -ct));
+    const float p_s = exp2_safe(__builtin_fmaf(xs[k], kLog2e, -cs));
+    g[k] = gscale * (p_s - p_t);
+  }
+  uint32_t o[4];
+  if (finite) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = bf16x2_rne_nonnan(g[2 * q], g[2 * q + 1]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = bf16_rne(g[2 * q]) | (bf16_rne(g[2 * q + 1]) << 16);
+  }
+  const u32x4 ov = {o[0], o[1], o[2], o[3]};
+  __builtin_amdgcn_raw_buffer_store_b128(ov, out, (int)off, 0, kNt);
+}
+
+// A window of at most n chunks from chunk c of a row on, as a buffer: loads past its end give
+// zeros, stores there are dropped.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const uint16_t* row, int64_t c,
+                                                         int64_t chunks, int n) {
+  const int64_t left = chunks - c;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(row + c * 8), (short)0,
+                                           left <= 0 ? 0 : (int)(left < n ? left : n) * 16, 0x27000);
+}
+
+__device__ __forceinline__ uint4 load_chunk(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+// Folds lanes 0 .. N - 1 into lane 0 (N a power of two) by halving offsets.
+template <int N>
+__device__ __forceinline__ void merge_lanes(int lane, Stat& st, Stat& ss, ArgMax& at, ArgMax& as) {
+#pragma unroll
+  for (int off = N / 2; off >= 1; off >>= 1) {
     Stat ot{__shfl_down(st.m, off, 64), __shfl_down(st.S, off, 64), __shfl_down(st.Q, off, 64)};
     Stat os{__shfl_down(ss.m, off, 64), __shfl_down(ss.S, off, 64), 0.0f};
     ArgMax oa{__shfl_down(at.v, off, 64), (int64_t)__shfl_down((long long)at.i, off, 64)};
     ArgMax ob{__shfl_down(as.v, off, 64), (int64_t)__shfl_down((long long)as.i, off, 64)};
-    if (lane + off < 64) {
+    if (lane + off < N) {
       st = merge(st, ot);
       ss = merge(ss, os);
       at = amax_merge(at, oa);
       as = amax_merge(as, ob);
     }
   }
-  if (lane == 0) {
-    sm_t[wv] = st.m; sS_t[wv] = st.S; sQ[wv] = st.Q; sm_s[wv] = ss.m; sS_s[wv] = ss.S;
-    sva[wv] = at.v; sia[wv] = at.i; svb[wv] = as.v; sib[wv] = as.i;
-  }
-  __syncthreads();
-  if (t == 0) {
-    Stat T{sm_t[0], sS_t[0], sQ[0]}, Sx{sm_s[0], sS_s[0], 0.0f};
-    ArgMax A{sva[0], sia[0]}, B{svb[0], sib[0]};
-    for (int w = 1; w < NW; ++w) {
-      T = merge(T, Stat{sm_t[w], sS_t[w], sQ[w]});
-      Sx = merge(Sx, Stat{sm_s[w], sS_s[w], 0.0f});
-      A = amax_merge(A, ArgMax{sva[w], sia[w]});
-      B = amax_merge(B, ArgMax{svb[w], sib[w]});
+}
+
+__device__ __forceinline__ float first_lane(float v) {
+  return as_f32((uint32_t)__builtin_amdgcn_readfirstlane((int)__builtin_bit_cast(uint32_t, v)));
+}
+
+__device__ __forceinline__ int64_t first_lane(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+  return ((int64_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | lo;
+}
+
+// Makes v's registers opaque: its unpacked halves are not carried along beside it.
+__device__ __forceinline__ void pin(uint4& v) {
+  asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+}
+
+// GRAD: a gradient is written, and the row's chunks are kept for it.
+template <int NT, bool GRAD>
+__global__ __launch_bounds__(NT, 4) void qad_kl_kernel(
+    const uint16_t* __restrict__ zt, int64_t ldt, const uint16_t* __restrict__ zs, int64_t lds_,
+    int64_t L, int64_t V, float gscale, float* __restrict__ row_kl, uint16_t* __restrict__ grad,
+    int64_t ldg, int32_t* __restrict__ agree) {
+  constexpr int NW = NT / 64;
+  constexpr int KR = GRAD ? kKeepReg : 0, KL = GRAD ? kKeepLds : 0;
+  __shared__ uint4 keep[KL ? KL * 2 * NT : 1];
+  __shared__ WaveStat part[2][NW];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int64_t chunks = V >> 3;
+
+  // Lane t owns chunks t, t + NT, t + 2 NT, ... of a row: the first KR pairs stay in registers,
+  // the next KL go to LDS (nobody else touches a lane's LDS), the rest is read again for the
+  // gradient.  All but the register part moves through two staging pairs.
+  uint4 rt[KR ? KR : 1], rs[KR ? KR : 1], vt[2], vs[2];
+  constexpr int kStep = NT * 16;                      // bytes from a lane's chunk to its next
+  constexpr int kKeep = (KR + KL) * NT;
+  uint32_t off = t * 16;
+  int head = (int)(chunks < kKeep ? chunks : kKeep);  // chunks of the kept part
+  {
+#pragma unroll
+    for (int j = 0; j < KR; ++j) {
+      rt[j] = load_chunk(window(zt + blockIdx.x * ldt, 0, chunks, kKeep), off + j * kStep);
+      rs[j] = load_chunk(window(zs + blockIdx.x * lds_, 0, chunks, kKeep), off + j * kStep);
     }
-    const float ct = T.m + __builtin_amdgcn_logf(T.S);     // base-2 log-sum-exp
-    const float cs = Sx.m + __builtin_amdgcn_logf(Sx.S);
-    row_kl[row] = T.Q / T.S + (cs - ct) * kLn2;
-    if (agree) agree[row] = A.i == B.i ? 1 : 0;
-    row_c[0] = ct;
-    row_c[1] = cs;
   }
-  if (!grad) return;
-  __syncthreads();
-  const float ct = row_c[0], cs = row_c[1];
-  uint16_t* pg = grad + row * ldg;
-  // Finite row statistics make every probability finite, so the hardware bf16 pack rounds
-  // exactly as bf16_rne; rows with non-finite logits keep the bit-level rounding (uniform per
-  // workgroup).
-  const bool finite = __builtin_isfinite(ct) && __builtin_isfinite(cs);
-  for (int64_t c0 = t; c0 < chunks; c0 += (int64_t)NT * kUnroll) {
-    uint4 vt[kUnroll], vs[kUnroll];
+  int par = 0;
+  for (int64_t row = blockIdx.x; row < L; row += gridDim.x, par ^= 1) {
+    // opaque: conditions and offsets of the unrolled parts are not carried in registers
+    asm volatile("" : "+s"(head), "+v"(off));
+    const uint16_t* pt = zt + row * ldt;
+    const uint16_t* ps = zs + row * lds_;
+    Stat st{-__builtin_huge_valf(), 0.0f, 0.0f};
+    Stat ss{-__builtin_huge_valf(), 0.0f, 0.0f};
+    LaneMax lt{-__builtin_huge_valf(), 0}, ls{-__builtin_huge_valf(), 0};
+    auto stage = [&](int u, int64_t b) __attribute__((always_inline)) {
+      vt[u] = load_chunk(window(pt, b, chunks, NT), off);
+      vs[u] = load_chunk(window(ps, b, chunks, NT), off);
+    };
+    stage(0, KR * NT);
+    stage(1, (KR + 1) * NT);
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int64_t c = c0 + (int64_t)u * NT;
-      vt[u] = make_uint4(0, 0, 0, 0);
-      vs[u] = make_uint4(0, 0, 0, 0);
-      if (c < chunks) {
-        vt[u] = *reinterpret_cast<const uint4*>(pt + c * 8);
-        vs[u] = *reinterpret_cast<const uint4*>(ps + c * 8);
-      }
+    for (int j = 0; j < KR; ++j) {
+      if (t < head - j * NT) fold_chunk(rt[j], rs[j], j, st, ss, lt, ls);
+      __builtin_amdgcn_sched_barrier(0);              // one chunk's temporaries at a time
+      pin(rt[j]);
+      pin(rs[j]);
     }
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int64_t c = c0 + (int64_t)u * NT;
-      if (c >= chunks) break;
-      float xt[8], xs[8], g[8];
-      unpack8_f32(vt[u], xt);
-      unpack8_f32(vs[u], xs);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float p_t = exp2_safe(__builtin_fmaf(xt[k], kLog2e, -ct));
-        const float p_s = exp2_safe(__builtin_fmaf(xs[k], kLog2e, -cs));
-        g[k] = gscale * (p_s - p_t);
+    for (int j = 0; j < KL; ++j) {
+      const int b = (KR + j) * NT, u = j & 1;
+      if (t < head - b) {
+        keep[2 * j * NT + t] = vt[u];
+        keep[(2 * j + 1) * NT + t] = vs[u];
+        fold_chunk(vt[u], vs[u], KR + j, st, ss, lt, ls);
       }
-      uint32_t o[4];
-      if (finite) {
+      __builtin_amdgcn_sched_barrier(0);
+      stage(u, b + 2 * NT);
+    }
+    static_assert(kKeepLds % 2 == 0, "the staging pairs alternate");
+    uint32_t i = KR + KL;
+    for (int64_t b = (KR + KL) * NT; b < chunks; b += 2 * NT, i += 2) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = bf16x2_rne_nonnan(g[2 * q], g[2 * q + 1]);
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = bf16_rne(g[2 * q]) | (bf16_rne(g[2 * q + 1]) << 16);
+      for (int u = 0; u < 2; ++u) {
+        if (t < chunks - b - u * NT) fold_chunk(vt[u], vs[u], i + u, st, ss, lt, ls);
+        __builtin_amdgcn_sched_barrier(0);
+        stage(u, b + (u + 2) * NT);
       }
-      const u32x4 ov = {o[0], o[1], o[2], o[3]};
-      __builtin_nontemporal_store(ov, reinterpret_cast<u32x4*>(pg + c * 8));
+    }
+
+    if (GRAD) {                                       // the part that was not kept, once more
+      stage(0, (KR + KL) * NT);
+      stage(1, (KR + KL + 1) * NT);
+    }
+    // a lane that saw nothing above the initial value has no chunk
+    auto in_row = [&](LaneMax m) __attribute__((always_inline)) {
+      return ArgMax{m.v, m.v == -__builtin_huge_valf() ? INT64_MAX : (int64_t)m.i * NT + t};
+    };
+    ArgMax at = in_row(lt), as = in_row(ls);
+    // workgroup merge in a fixed tree: within each wave by halving offsets, then (every wave for
+    // itself) over the waves in the same way.  The rows alternate between two sets of LDS words:
+    // a wave writes a set again only after the next row's barrier, so one barrier a row does.
+    merge_lanes<64>(lane, st, ss, at, as);
+    if (lane == 0) {
+      part[par][wv] = WaveStat{st, ss, at, as};
+    }
+    __syncthreads();
+    const WaveStat& o = part[par][lane < NW ? lane : 0];
+    st = o.st;
+    ss = o.ss;
+    at = o.at;
+    as = o.as;
+    merge_lanes<NW>(lane, st, ss, at, as);
+    const float ct = first_lane(st.m + __builtin_amdgcn_logf(st.S));   // base-2 log-sum-exp
+    const float cs = first_lane(ss.m + __builtin_amdgcn_logf(ss.S));
+    if (t == 0) row_kl[row] = st.Q / st.S + (cs - ct) * kLn2;
+    if (agree) {
+      // The maxima's first chunks; where that is one chunk, its owner looks at the elements (before
+      // it writes a gradient there).
+      const int64_t it = first_lane(at.i), is = first_lane(as.i);
+      if (it != is || it >= chunks) {
+        if (t == 0) agree[row] = it == is ? 1 : 0;
+      } else if (t == (int)(it & (NT - 1))) {
+        float xt[8], xs[8];
+        unpack8_f32(*reinterpret_cast<const uint4*>(pt + it * 8), xt);
+        unpack8_f32(*reinterpret_cast<const uint4*>(ps + it * 8), xs);
+        agree[row] = first_eq8(xt, max8(xt)) == first_eq8(xs, max8(xs)) ? 1 : 0;
+      }
+    }
+    if (GRAD) {
+      uint16_t* pg = grad + row * ldg;
+      const bool finite = __builtin_isfinite(ct) && __builtin_isfinite(cs);
+      for (int64_t b = (KR + KL) * NT; b < chunks; b += 2 * NT) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          grad_chunk(vt[u], vs[u], ct, cs, gscale, finite, window(pg, b + u * NT, chunks, NT), off);
+          __builtin_amdgcn_sched_barrier(0);
+          stage(u, b + (u + 2) * NT);
+        }
+      }
+      asm volatile("" : "+s"(head), "+v"(off));
+      const auto wg = window(pg, 0, chunks, kKeep);
+#pragma unroll
+      for (int j = 0; j < KL; ++j) {
+        if ((KR + j) * NT < head)                     // uniform
+          grad_chunk(keep[2 * j * NT + t], keep[(2 * j + 1) * NT + t], ct, cs, gscale, finite, wg,
+                     off + (KR + j) * kStep);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // each register pair is refilled from the next row as soon as it is free
+      const int64_t next = row + gridDim.x;
+      const auto wt = window(zt + next * ldt, 0, next < L ? chunks : 0, kKeep);
+      const auto ws = window(zs + next * lds_, 0, next < L ? chunks : 0, kKeep);
+#pragma unroll
+      for (int j = 0; j < KR; ++j) {
+        if (j * NT < head) grad_chunk(rt[j], rs[j], ct, cs, gscale, finite, wg, off + j * kStep);
+        __builtin_amdgcn_sched_barrier(0);
+        rt[j] = load_chunk(wt, off + j * kStep);
+        rs[j] = load_chunk(ws, off + j * kStep);
+      }
     }
   }
 }
@@ -258,8 +386,16 @@ hipError_t launch_qad_kl(const uint16_t* zt, int64_t ldt, const uint16_t* zs, in
                          int64_t L, int64_t V, float gscale, float* row_kl, float* loss,
                          uint16_t* grad, int64_t ldg, int32_t* agree, hipStream_t s) {
   if (L > 0) {
-    hipLaunchKernelGGL(qad_kl_kernel<1024>, dim3((unsigned)L), dim3(1024), 0, s, zt, ldt, zs, lds_,
-                       V, gscale, row_kl, grad, ldg, agree);
+    // Two 512-lane workgroups a unit where they keep most of a row (against one of 1024, us: 8192 x
+    // 32000 328 / 416, 2048 x 49152 127 / 148, 2048 x 65536 169 / 182, 2048 x 100000 272 / 273, 4096 x
+    // 151936 863 / 797).
+    const bool wide = V > 65536;
+    auto* k = !grad ? &qad_kl_kernel<1024, false>
+              : wide ? &qad_kl_kernel<1024, true> : &qad_kl_kernel<512, true>;
+    const int64_t slots = wide ? kCUs : 2 * kCUs;
+    hipLaunchKernelGGL(k, dim3((unsigned)(grad && L > slots ? slots : L)),
+                       dim3(grad && !wide ? 512 : 1024), 0, s, zt, ldt, zs, lds_, L, V, gscale,
+                       row_kl, grad, ldg, agree);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -58,6 +58,34 @@ def test_qad_kl_matches_oracle(qf, L, V, pad):
     _check(got, oracle.qad_kl(d["zt"], d["zs"]), f"L={L} V={V}")
 
 
+@pytest.mark.parametrize("L,V", [
+    (3, 8 * 512), (3, 8 * 512 * 8 - 8), (2, 8 * 512 * 8 + 8), (2, 8 * 512 * 12), (2, 8 * 512 * 12 + 8),
+    (3, 65536), (2, 65544), (2, 8 * 1024 * 12 - 8), (2, 8 * 1024 * 13 + 8), (2, 8 * 1024 * 14),
+    (1100, 520), (260, 65544)])
+def test_qad_kl_kept_parts_and_row_walk(qf, L, V):
+    """The ends of what a lane keeps in registers and in LDS, for both workgroup sizes, and more
+    rows than workgroups; the maxima of some rows are tied with an element at the ends.
+
+    Gradient: a probability is 2^(a - c), c = log2 of the sum (below 64: half an ulp is 2^-19,
+    1.3e-6 of the probability) and the sum itself good to about 1e-6, so each is within 4e-6 of
+    its own value; their difference, however small, is then rounded to bf16."""
+    d = workloads.qad_logits(L + V, L, V)
+    zt, zs = d["zt"].copy(), d["zs"].copy()
+    for z in (zt, zs):
+        top = z[np.arange(L), bf16_to_f64(z).argmax(1)]
+        z[::2, V - 1 if V % 16 else V - 2] = top[::2]
+        z[1::3, 0] = top[1::3]
+    kl, loss, grad, agree = _run(qf, zt, zs)
+    ref = oracle.qad_kl(zt, zs)
+    _check((kl, loss, None, agree), ref, f"L={L} V={V}")
+    p = 0.0
+    for z in (bf16_to_f64(zt), bf16_to_f64(zs)):
+        e = np.exp(z - z.max(1, keepdims=True))
+        p = p + e / e.sum(1, keepdims=True)
+    err = np.abs(bf16_to_f64(grad) - ref[2])
+    assert np.all(err <= 2.0 ** -8 * np.abs(ref[2]) + 4e-6 * p / L)
+
+
 def test_qad_kl_ties_and_identical_rows(qf):
     rng = np.random.default_rng(4)
     L, V = 16, 512
