@@ -711,10 +711,20 @@ qf_status check_grouped(const char* fn, const qf_grouped_desc* d, const int64_t*
   return QF_OK;
 }
 
-// W_hat (and, with pk, the experts' packed W_hat in the same launch) and A_hat.
+// The forward decodes the packed experts inside the GEMM: the packed operand is written anyway
+// (saved), no backward takes W_hat from the workspace (QF_FLAG_REUSE_WS), and an expert has few
+// rows, so that a weight tile is decoded about once.  Same bits.
+bool grouped_fused_forward(const qf_grouped_desc* d, const void* saved) {
+  return saved != nullptr && (d->flags & QF_FLAG_REUSE_WS) == 0 &&
+         qf::grouped_packed_b_ok(d->wfmt, d->E, d->T, d->K);
+}
+
+// W_hat (unless packed_only; with pk, the experts' packed W_hat in the same launch) and A_hat.
 qf_status grouped_quantize(const qf_grouped_desc* d, const uint16_t* X, const uint16_t* W,
                            const GroupedWs& g, bool do_w, bool do_a, const uint16_t** Wop,
-                           const uint16_t** Aop, hipStream_t s, const Packed* pk = nullptr) {
+                           const uint16_t** Aop, hipStream_t s, const Packed* pk = nullptr,
+                           bool packed_only = false) {
+  uint16_t* const what = packed_only ? nullptr : g.what;
   *Wop = W;
   *Aop = X;
   const int64_t R = d->N, K = d->K;
@@ -728,16 +738,16 @@ qf_status grouped_quantize(const qf_grouped_desc* d, const uint16_t* X, const ui
             QF_TRY(dev(qf::launch_amax_batched(W, d->E, R, K, g.wamax, false, s), "amax"));
             gp = g.wamax;
           }
-          QF_TRY(dev(qf::launch_nvfp4_batched(W, d->E, R, K, gp, q.S, q.codes, q.scales, g.what,
+          QF_TRY(dev(qf::launch_nvfp4_batched(W, d->E, R, K, gp, q.S, q.codes, q.scales, what,
                                               s),
                      "nvfp4"));
           break;
         }
         case QF_FMT_MXFP4:
-          QF_TRY(dev(qf::launch_mxfp4(W, d->E * R, K, K, q.codes, q.scales, g.what, s), "mxfp4"));
+          QF_TRY(dev(qf::launch_mxfp4(W, d->E * R, K, K, q.codes, q.scales, what, s), "mxfp4"));
           break;
         case QF_FMT_Q4K:
-          QF_TRY(dev(qf::launch_q4k(W, d->E * R, K, K, q.codes, g.what, s), "q4k"));
+          QF_TRY(dev(qf::launch_q4k(W, d->E * R, K, K, q.codes, what, s), "q4k"));
           break;
       }
     }
@@ -780,9 +790,18 @@ qf_status qf_qlinear_grouped_fwd(const qf_grouped_desc* d, const int64_t* group_
   GroupedWs g = grouped_ws(d, ws);
   const uint16_t *Wop, *Aop;
   const Packed pk = saved ? grouped_saved_layout(d, saved) : Packed{};
-  QF_TRY(grouped_quantize(d, X, W, g, true, true, &Wop, &Aop, s, saved ? &pk : nullptr));
-  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, g.tile_start, g.order, g.kstart, s),
+  const bool fused = grouped_fused_forward(d, saved);
+  QF_TRY(grouped_quantize(d, X, W, g, true, true, &Wop, &Aop, s, saved ? &pk : nullptr, fused));
+  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, qf::grouped_tile_rows(d->E, d->T),
+                                     g.tile_start, g.order, g.kstart, s),
              "prep"));
+  if (fused) {
+    QF_TRY(dev(qf::launch_grouped_nt_rows_packed_b(d->E, d->T, d->N, d->K, group_offsets,
+                                                   g.tile_start, Aop, d->K, d->wfmt, pk.codes,
+                                                   pk.scales, pk.S, Y, d->N, s),
+               "grouped forward"));
+    return ok();
+  }
   QF_TRY(dev(qf::launch_grouped_nt_rows(d->E, d->T, d->N, d->K, group_offsets, g.tile_start, Aop,
                                         d->K, Wop, d->K, d->N * d->K, Y, d->N, s),
              "grouped forward"));
@@ -812,14 +831,15 @@ qf_status qf_qlinear_grouped_bwd_ste(const qf_grouped_desc* d, const int64_t* gr
   const uint16_t *Wop, *Aop;
   QF_TRY(grouped_quantize(d, X, W, g, !reuse && dX && !fuse_w && !from_saved, false, &Wop,
                           &Aop, s));
-  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, g.tile_start, g.order, g.kstart, s),
+  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, qf::grouped_tile_rows(d->E, d->T),
+                                     g.tile_start, g.order, g.kstart, s),
              "prep"));
   // dY^T in the padded layout of dW is written by the dX launch from the dY tiles it stages
-  // when both gradients are asked for and dX spans at least 8 tile columns (K >= 1793);
-  // otherwise by the grouped transposer
+  // when both gradients are asked for, its tiles have 256 rows and it spans at least 8 tile columns
+  // (K >= 1793); otherwise by the grouped transposer
   const int64_t tp = grouped_tpad(d), ldt = ws_ld(tp);
   const bool dyt_by_dx = dX != nullptr && dW != nullptr && (d->K + 255) / 256 >= 8 &&
-                         ldt < qf::kGemmAtMaxLd;
+                         ldt < qf::kGemmAtMaxLd && qf::grouped_tile_rows(d->E, d->T) == 256;
   if (dX) {
     if (from_saved) {
       const Packed pk = grouped_saved_layout(d, const_cast<void*>(saved));
@@ -1365,7 +1385,8 @@ qf_status qf_qlinear_grouped_lora_fwd(const qf_grouped_desc* d, const qf_lora* l
     QF_TRY(dev(qf::launch_mxfp4(X, d->T, d->K, d->K, nullptr, nullptr, g.ahat, s), "mxfp4"));
     Aop = g.ahat;
   }
-  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, g.tile_start, g.order, nullptr, s),
+  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, qf::grouped_tile_rows(d->E, d->T),
+                                     g.tile_start, g.order, nullptr, s),
              "prep"));
   QF_TRY(dev(qf::launch_grouped_nt_rows(d->E, d->T, d->N, d->K, group_offsets, g.tile_start, Aop,
                                         d->K, g.what, d->K, d->N * d->K, Y, d->N, s),
@@ -1395,7 +1416,8 @@ qf_status qf_qlinear_grouped_lora_bwd_ste(const qf_grouped_desc* d, const qf_lor
   const bool reuse = (d->flags & QF_FLAG_REUSE_WS) != 0;
   const int64_t E = d->E, T = d->T, N = d->N, K = d->K, r = lora->r, rp = (r + 15) / 16 * 16;
   if (dX) {
-    QF_TRY(dev(qf::launch_grouped_prep(group_offsets, E, g.tile_start, g.order, nullptr, s),
+    QF_TRY(dev(qf::launch_grouped_prep(group_offsets, E, qf::grouped_tile_rows(E, T), g.tile_start,
+                                       g.order, nullptr, s),
                "prep"));
     if (reuse) {
       QF_TRY(dev(qf::launch_transpose_bf16(g.what, N, K, K, g.whatt, N, E, N * K, N * K, s),

@@ -7,7 +7,8 @@
 //   dX          = dY W_hat             A = dY [M, N],      B = W_hat^T [K, N]
 //   dW          = dY^T A_hat           A = dY^T [N, M],    B = A_hat^T [K, M]
 //
-// Design (256 x 256 block tile, 256 x 128 where that fills the chip better):
+// Design (256 x 256 block tile, 256 x 128 where that fills the chip better, 128 x 256 for experts
+// with few rows):
 //  - 4 wavefronts, one per SIMD, each owning a 128 x 128 (128 x 64) sub-tile as 16 x 16
 //    v_mfma_f32_16x16x32_bf16 accumulators (256 / 128 AGPRs).  What bounds the full launches is
 //    power: the chip holds 1.97 GHz in a loop of these against 1.70 GHz in one of
@@ -95,10 +96,10 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // TM x TN: 16 x 16 accumulator blocks of a wavefront's sub-tile; the 2 x 2 wavefronts of a
-// workgroup own a 32 TM x 32 TN tile (8 x 8: 256 x 256; 8 x 4: 256 x 128).
+// workgroup own a 32 TM x 32 TN tile (8 x 8: 256 x 256; 8 x 4: 256 x 128; 4 x 8: 128 x 256).
 //
-// BQ != 0 (QF_FMT_NVFP4 / MXFP4 / Q4K; 256 x 256 tile, dense, bf16 C): B is the
-// packed quantized weight instead of a bf16 matrix.  Each lane owns one B row of its
+// BQ != 0 (QF_FMT_NVFP4 / MXFP4 / Q4K; 256-column tile, dense or per expert, bf16 C): B is the
+// packed quantized weight (the experts' back to back) instead of a bf16 matrix.  Each lane owns one B row of its
 // wavefront's 64 (row 64 w + lane) and, one step ahead, loads that row's codes and scales for
 // a stage into registers (32 bytes of codes plus 4 / 2 scale bytes, or the Q4_K block's 16-byte
 // header and 32 code bytes); in the next step it decodes them with the quantizers' own decode
@@ -120,9 +121,10 @@ __device__ __forceinline__ void static_for(F&& f) {
 template <bool C_F32, int MODE, int TM, int TN, int BQ = 0, bool BF = false, bool AT2 = false,
           bool PF = false>
 __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
-  static_assert(TM == 8 && (TN == 8 || TN == 4), "256-row tiles of 256 or 128 columns");
-  static_assert(BQ == 0 || (TN == 8 && MODE == kDense && !C_F32),
-                "packed B: the dense 256 x 256 bf16 form");
+  static_assert((TM == 8 && (TN == 8 || TN == 4)) || (TM == 4 && TN == 8 && MODE == kGroupRows),
+                "256-row tiles of 256 or 128 columns; per expert also 128 rows by 256 columns");
+  static_assert(BQ == 0 || (TN == 8 && (MODE == kDense || MODE == kGroupRows) && !C_F32),
+                "packed B: 256-column bf16 forms without A^T");
   static_assert(!BF || (TN == 8 && BQ == 0 && (MODE == kDense || MODE == kDenseAT)),
                 "fragment-major B: the dense 256 x 256 forms");
   constexpr int BM = 32 * TM, BN = 32 * TN;
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
   // stage s+1's loads: L0 in the second slice of step s-1, the rest in the first of step s
   // (fragment-major B: all of A's in the latter)
   constexpr int L0 = BF ? 0 : AT || BQ != 0 ? NLD / 2 : NLD / 4 * 3;
-  constexpr int CSTEP = TN / 2;                  // MFMAs per copy issued
+  constexpr int CSTEP = TM == 4 ? 2 : TN / 2;    // MFMAs per copy issued
   static_assert((L0 > NLD - L0 ? L0 : NLD - L0) * CSTEP <= TM * TN, "a slice holds its copies");
   // stages between a prefetch and the stage being multiplied: us with 2 / 3 / 4, FP32 6144 x 4096
   // x 32768 1281 / 1192 / 1171, writing A^T 32768 x 4096 x 24576 4518 / 4561 / 4580, the expert
@@ -162,6 +164,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
   int64_t m0, m_end, n0;
   int ks0 = 0, ks1 = (int)(p.K / BK);            // stage range of this item
   int64_t cofs = 0;                              // element offset of this item's C
+  int64_t bq_e = 0;                              // expert of this item (packed B)
   // A^T columns of this tile's first row and the end of its A^T range: rows whose column is
   // below at_end but lie past the operand get zeros (grouped padding)
   int64_t at_col0 = 0, at_end = 0;
@@ -211,6 +214,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
       at_end = 64 * (int64_t)p.kstart[lo + 1];
     }
     Bp += (int64_t)lo * p.bstride;
+    bq_e = lo;
   }
   const int64_t n_end = p.N, K = p.K;
 
@@ -271,14 +275,14 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
   const uint8_t* bq_srow = nullptr;
   float bq_S = 0.0f;
   if (BQ != 0) {
-    const int64_t gr = n0 + brow < n_end ? n0 + brow : n_end - 1;
+    const int64_t gr = bq_e * n_end + (n0 + brow < n_end ? n0 + brow : n_end - 1);
     if (BQ == QF_FMT_Q4K) {
       bq_row = p.bq_codes + gr * (K / 256) * 144;
     } else {
       bq_row = p.bq_codes + gr * (K / 2);
       bq_srow = p.bq_scales + gr * (K / (BQ == QF_FMT_NVFP4 ? 16 : 32));
     }
-    if (BQ == QF_FMT_NVFP4) bq_S = p.bq_S[0];    // the quantizer's S = fl(g / 2688)
+    if (BQ == QF_FMT_NVFP4) bq_S = p.bq_S[bq_e];    // the quantizer's S = fl(g / 2688)
   }
   auto bq_load = [&](int64_t se, BqRegs& r) __attribute__((always_inline)) {
     if (BQ == QF_FMT_Q4K) {
@@ -340,7 +344,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
   //          the write.
   // The arithmetic is the decode functions' (codec::*_decode8), split up.
   float bq_D = 0.0f, bq_d = 0.0f, bq_dmin = 0.0f, bq_t1[2] = {0.0f, 0.0f}, bq_t2[2] = {0.0f, 0.0f};
-  uint32_t bq_o[4] = {0, 0, 0, 0}, bq_qw[2] = {0, 0}, bq_e = 0;
+  uint32_t bq_o[4] = {0, 0, 0, 0}, bq_qw[2] = {0, 0}, bq_x = 0;
   auto bq_word = [&](const BqRegs& r, int c) __attribute__((always_inline)) -> uint32_t {
     switch (c) {
       case 0: return r.c0.x; case 1: return r.c0.y; case 2: return r.c0.z; case 3: return r.c0.w;
@@ -376,8 +380,8 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
     } else if (BQ == QF_FMT_MXFP4) {
       const int c = u / 3, k = u % 3;
       const uint32_t cw = bq_word(r, c);
-      if (k == 0) bq_e = (r.sc >> (8 * (c >> 2))) & 0xFFu;
-      const float sc = codec::e8m0_scale(bq_e);
+      if (k == 0) bq_x = (r.sc >> (8 * (c >> 2))) & 0xFFu;
+      const float sc = codec::e8m0_scale(bq_x);
       if (k == 0) {
         bq_o[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(cw, sc, 0));
         bq_o[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(cw, sc, 1));
@@ -385,7 +389,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
         bq_o[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(cw, sc, 2));
         bq_o[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(cw, sc, 3));
       } else {
-        const bool nan = bq_e == 0xFFu;                // (codec::mxfp4_decode8's NaN block)
+        const bool nan = bq_x == 0xFFu;                // (codec::mxfp4_decode8's NaN block)
 #pragma unroll
         for (int q = 0; q < 4; ++q) bq_o[q] = nan ? 0x7FC07FC0u : bq_o[q];
         bq_store(c, buf);
@@ -667,6 +671,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
     // wait); stage s+1's second half is decoded into buffer nxt in slice 0, stage s+2's first
     // half into buffer cur in slice 1 (slot g of 24: the g-th decode operation of the half).
     constexpr int kBqHalf = BQ == QF_FMT_NVFP4 ? 24 : BQ == QF_FMT_MXFP4 ? 12 : 23;
+    constexpr int BSTEP = NM / 32;               // MFMAs per decode operation
     auto bf_hook = [&](int kk, int t) __attribute__((always_inline)) {
       // after MFMA t = NM - TN + j, the last one using fbr[kk][j], that register is loaded with
       // stage s+1's fragment (not in the last step)
@@ -675,8 +680,8 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
     auto hook0 = [&](int t) __attribute__((always_inline)) {
       if (BQ != 0) {
         if (t == 1) bq_load(e_nx2, bq_nxt);
-        const int g = t / 2 + kBqHalf;
-        if (LD1 && t % 2 == 0 && g < kBqOps) bq_op(bq_cur, e_nx1, g, nxt);
+        const int g = t / BSTEP + kBqHalf;
+        if (LD1 && t % BSTEP == 0 && g < kBqOps) bq_op(bq_cur, e_nx1, g, nxt);
       }
       at_hook0(t);
       if (BQ == 0 && t == 15 * H + 1) calc_nx2();
@@ -690,8 +695,8 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
     };
     auto hook1 = [&](int t) __attribute__((always_inline)) {
       if (BQ != 0) {
-        const int g = t / 2;
-        if (LD2 && t % 2 == 0 && g < kBqHalf) bq_op(bq_cur, e_nx2, g, cur);
+        const int g = t / BSTEP;
+        if (LD2 && t % BSTEP == 0 && g < kBqHalf) bq_op(bq_cur, e_nx2, g, cur);
       }
       at_hook1(t);
       bf_hook(1, t);
@@ -918,6 +923,12 @@ int vec_store_ok(const void* C, int64_t ldc, int esize) {
 
 }  // namespace
 
+// With few rows per expert half of a 256-row tile is padding.  The grouped layer's forward +
+// backward (NVFP4, saved operands; E x rows per expert, N x K), us, in 256- / 128-row tiles: 64 x 16,
+// 2048 x 2048 1014 / 973, 128 x 64, 3072 x 2048 2961 / 2809, 64 x 96, 2048 x 2048 1065 / 994; no gain
+// from 128 rows per expert on (128 x 128, 3072 x 3072 4632 / 4652, 128 x 187 4854 / 4954).
+int grouped_tile_rows(int64_t E, int64_t T) { return T <= 96 * E ? 128 : 256; }
+
 size_t gemm_nt_split_bytes(int64_t M, int64_t N) {
   const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
   return (size_t)(2 * std::min<int64_t>(tiles, kMaxSplitTiles)) * BM * BN * sizeof(float);
@@ -1135,19 +1146,57 @@ hipError_t launch_grouped_nt_rows(int64_t E, int64_t T, int64_t N, int64_t K, co
                         ldat >= kGemmAtMaxLd || reinterpret_cast<uintptr_t>(at) % 8 != 0))
     return hipErrorInvalidValue;
   if (T == 0 || N == 0 || E == 0) return hipSuccess;
-  if (!nt_offsets_fit(K, lda, ldb)) return hipErrorInvalidValue;
+  const int rows = grouped_tile_rows(E, T);
+  if ((at != nullptr && rows != BM) || !nt_offsets_fit(K, lda, ldb)) return hipErrorInvalidValue;
   NtArgs a{};
   a.A = A; a.B = B; a.C = C; a.lda = lda; a.ldb = ldb; a.ldc = ldc; a.bstride = bstride;
   a.M = T; a.N = N; a.K = K; a.off = off; a.tile_start = tile_start; a.E = (int)E;
   a.at = at; a.ldat = ldat; a.kstart = kstart;
   a.vec_store = vec_store_ok(C, ldc, 2);
   a.tiles_n = (int)((N + BN - 1) / BN);
-  a.tiles_m = (int)((T + BM - 1) / BM + E);
+  a.tiles_m = (int)((T + rows - 1) / rows + E);
   const int64_t per = ((int64_t)a.tiles_m * a.tiles_n + kXcds - 1) / kXcds;
   const dim3 grid((unsigned)(kXcds * per));
   if (at != nullptr && a.tiles_n < 16) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRowsAT, 8, 8, 0, false, true, true>), grid, dim3(256), 0, s, a);
   else if (at != nullptr) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRowsAT, 8, 8, 0, false, false, true>), grid, dim3(256), 0, s, a);
+  else if (rows == 128) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRows, 4, 8, 0, false, false, true>), grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRows, 8, 8, 0, false, false, true>), grid, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+// Few rows per expert: a weight tile is read about once, and W_hat need not be written and read
+// for that.  Forward, us, from W_hat / decoded here (128-row tiles): 64 x 16 rows, 2048 x 2048 NVFP4
+// 443 / 381, MXFP4 345 / 293; 128 x 64, 3072 x 2048 1325 / 1181 and 1042 / 959; 64 x 96, 2048 x 2048
+// 452 / 451 and 362 / 382.  Q4_K's longer decode does not pay (128 x 64: 1126 / 1186).
+bool grouped_packed_b_ok(int fmt, int64_t E, int64_t T, int64_t K) {
+  return (fmt == QF_FMT_NVFP4 || fmt == QF_FMT_MXFP4) && K > 0 && K % BK == 0 && T <= 64 * E &&
+         nt_offsets_fit(K, K, K);
+}
+
+hipError_t launch_grouped_nt_rows_packed_b(int64_t E, int64_t T, int64_t N, int64_t K,
+                                           const int64_t* off, const int* tile_start,
+                                           const uint16_t* A, int64_t lda, int bfmt,
+                                           const uint8_t* codes, const uint8_t* scales,
+                                           const float* S, uint16_t* C, int64_t ldc,
+                                           hipStream_t s) {
+  if (!grouped_packed_b_ok(bfmt, E, T, K) || codes == nullptr || scales == nullptr ||
+      (bfmt == QF_FMT_NVFP4 && S == nullptr))
+    return hipErrorInvalidValue;
+  if (T == 0 || N == 0 || E == 0) return hipSuccess;
+  if (!nt_offsets_fit(K, lda, K)) return hipErrorInvalidValue;
+  NtArgs a{};
+  a.A = A; a.B = nullptr; a.C = C; a.lda = lda; a.ldb = K; a.ldc = ldc;
+  a.M = T; a.N = N; a.K = K; a.off = off; a.tile_start = tile_start; a.E = (int)E;
+  a.bq_codes = codes; a.bq_scales = scales; a.bq_S = S;
+  a.vec_store = vec_store_ok(C, ldc, 2);
+  a.tiles_n = (int)((N + BN - 1) / BN);
+  a.tiles_m = (int)((T + 127) / 128 + E);
+  const int64_t per = ((int64_t)a.tiles_m * a.tiles_n + kXcds - 1) / kXcds;
+  const dim3 grid((unsigned)(kXcds * per)), b(256);
+  if (bfmt == QF_FMT_NVFP4)
+    hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRows, 4, 8, QF_FMT_NVFP4>), grid, b, 0, s, a);
+  else
+    hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRows, 4, 8, QF_FMT_MXFP4>), grid, b, 0, s, a);
   return hipGetLastError();
 }
 

@@ -8,15 +8,13 @@
 namespace qf {
 namespace {
 
-constexpr int BM = 256;   // row tile of the NT GEMM's grouped-rows mode
-
-__global__ void grouped_prep_kernel(const int64_t* __restrict__ off, int E, int* tile_start,
-                                    int* order, int* kstart) {
+__global__ void grouped_prep_kernel(const int64_t* __restrict__ off, int E, int tile_rows,
+                                    int* tile_start, int* order, int* kstart) {
   __shared__ int cnt[1024], cnt64[1024];
   const int e = threadIdx.x;
   int64_t rows = 0;
   if (e < E) rows = off[e + 1] - off[e];
-  if (e < E) cnt[e] = (int)((rows + BM - 1) / BM);
+  if (e < E) cnt[e] = (int)((rows + tile_rows - 1) / tile_rows);
   if (e < E) cnt64[e] = (int)((rows + 63) / 64);
   __syncthreads();
   if (e == 0) {
@@ -41,10 +39,10 @@ __global__ void grouped_prep_kernel(const int64_t* __restrict__ off, int E, int*
 
 }  // namespace
 
-hipError_t launch_grouped_prep(const int64_t* off, int64_t E, int* tile_start, int* order,
-                               int* kstart, hipStream_t s) {
-  hipLaunchKernelGGL(grouped_prep_kernel, dim3(1), dim3(1024), 0, s, off, (int)E, tile_start,
-                     order, kstart);
+hipError_t launch_grouped_prep(const int64_t* off, int64_t E, int tile_rows, int* tile_start,
+                               int* order, int* kstart, hipStream_t s) {
+  hipLaunchKernelGGL(grouped_prep_kernel, dim3(1), dim3(1024), 0, s, off, (int)E, tile_rows,
+                     tile_start, order, kstart);
   return hipGetLastError();
 }
 

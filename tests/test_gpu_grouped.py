@@ -65,6 +65,37 @@ def test_grouped_matches_per_expert_loop(qf, wfmt, afmt):
             assert np.all(dW[e] == 0.0)
 
 
+@pytest.mark.parametrize("wfmt,N,K", [("nvfp4", 264, 64), ("nvfp4", 520, 192), ("nvfp4", 264, 80),
+                                      ("mxfp4", 248, 320), ("mxfp4", 264, 96), ("q4k", 264, 768),
+                                      ("none", 256, 136)])
+def test_grouped_few_rows_per_expert(qf, wfmt, N, K):
+    """At most 96 rows per expert: 128-row tiles; at most 64, with a saved NVFP4 / MXFP4 operand and
+    K a multiple of 64: the forward decodes the packed experts (one stage, few stages, ragged N;
+    otherwise it reads W_hat).  Row counts around the tile edges; both forms against the oracle and
+    each other."""
+    rng = np.random.default_rng(N + K)
+    counts = np.array([0, 127, 1, 128, 300, 129, 0, 7, 0, 0, 256, 16, 0, 64, 0, 5, 0, 0])
+    E = len(counts)
+    offsets = np.concatenate([[0], np.cumsum(counts)])
+    T = int(offsets[-1])
+    X = workloads.normal_bf16(rng, (T, K))
+    W = np.stack([workloads.normal_bf16(rng, (N, K), 0.02 * (e + 1)) for e in range(E)])
+    dY = workloads.normal_bf16(rng, (T, N))
+    outs = [run_grouped(qf, offsets, X, W, dY, wfmt, "none", saved=sv) for sv in (True, False)]
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+    Y, dX, dW = outs[0]
+    for e in range(E):
+        r0, r1 = offsets[e], offsets[e + 1]
+        if r1 == r0:
+            assert np.all(dW[e] == 0.0)
+            continue
+        what = oracle.fakequant(W[e], wfmt)
+        assert_close(bf16_to_f64(Y[r0:r1]), oracle.linear_fwd(X[r0:r1], what), f"Y e={e}")
+        assert_close(bf16_to_f64(dX[r0:r1]), oracle.linear_dx(dY[r0:r1], what), f"dX e={e}")
+        assert_close(dW[e].astype(np.float64), oracle.linear_dw(dY[r0:r1], X[r0:r1]), f"dW e={e}")
+
+
 def test_grouped_dw_tile_grid_split_over_xcds(qf):
     """Per-expert dW grids of 5 x 3 tiles (ragged in both dimensions) are dealt to the 8 XCDs
     in shares of 1 or 2 tiles; every expert's gradient is complete, empty experts are zero."""
