@@ -283,8 +283,10 @@ QF_API qf_status qf_qlinear_grouped_fwd(const qf_grouped_desc* d, const int64_t*
  * qf_qlinear_grouped_bwd_ste -- per expert: dX_e = dY_e W_hat_e (bf16 [T, K], may be NULL),
  *   dW_e = dY_e^T A_hat_e (FP32 [E, N, K], may be NULL; experts with no rows get zeros).
  *   saved: the forward's saved buffer (the experts' W_hat^T are dequantized from it: no amax
- *   pass, no re-quantization), or NULL (W is quantized again, or with QF_FLAG_REUSE_WS, in both
- *   calls' descriptors where the forward had a saved buffer, the workspace's W_hat is used).  The gradients are bit-identical either way.
+ *   pass, no re-quantization), or NULL: W is quantized again, or with QF_FLAG_REUSE_WS the
+ *   workspace's W_hat is used (with up to 64 rows per expert and NVFP4 or MXFP4, where a forward
+ *   may decode the experts without writing W_hat, W is quantized again with the workspace's amax).
+ *   The gradients are bit-identical either way, whether or not the forward had a saved buffer.
  */
 QF_API qf_status qf_qlinear_grouped_bwd_ste(const qf_grouped_desc* d, const int64_t* group_offsets,
                                      const uint16_t* dY, const uint16_t* X, const uint16_t* W,

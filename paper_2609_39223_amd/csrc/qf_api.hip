@@ -711,12 +711,12 @@ qf_status check_grouped(const char* fn, const qf_grouped_desc* d, const int64_t*
   return QF_OK;
 }
 
-// The forward decodes the packed experts inside the GEMM: the packed operand is written anyway
-// (saved), no backward takes W_hat from the workspace (QF_FLAG_REUSE_WS), and an expert has few
-// rows, so that a weight tile is decoded about once.  Same bits.
-bool grouped_fused_forward(const qf_grouped_desc* d, const void* saved) {
-  return saved != nullptr && (d->flags & QF_FLAG_REUSE_WS) == 0 &&
-         qf::grouped_packed_b_ok(d->wfmt, d->E, d->T, d->K);
+// The forward decodes the packed experts inside the GEMM where it writes the packed operand anyway
+// (saved) and an expert has few rows, so that a weight tile is decoded about once.  Same bits, but
+// no W_hat in the workspace: whether there is one depends on an argument that the backward does
+// not see, so a QF_FLAG_REUSE_WS backward of such a layer never takes W_hat from there.
+bool grouped_decodes_experts(const qf_grouped_desc* d) {
+  return qf::grouped_packed_b_ok(d->wfmt, d->E, d->T, d->K);
 }
 
 // W_hat (unless packed_only; with pk, the experts' packed W_hat in the same launch) and A_hat.
@@ -790,7 +790,7 @@ qf_status qf_qlinear_grouped_fwd(const qf_grouped_desc* d, const int64_t* group_
   GroupedWs g = grouped_ws(d, ws);
   const uint16_t *Wop, *Aop;
   const Packed pk = saved ? grouped_saved_layout(d, saved) : Packed{};
-  const bool fused = grouped_fused_forward(d, saved);
+  const bool fused = saved != nullptr && grouped_decodes_experts(d);
   QF_TRY(grouped_quantize(d, X, W, g, true, true, &Wop, &Aop, s, saved ? &pk : nullptr, fused));
   QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, qf::grouped_tile_rows(d->E, d->T),
                                      g.tile_start, g.order, g.kstart, s),
@@ -825,9 +825,11 @@ qf_status qf_qlinear_grouped_bwd_ste(const qf_grouped_desc* d, const int64_t* gr
   GroupedWs g = grouped_ws(d, ws);
   const bool reuse = (d->flags & QF_FLAG_REUSE_WS) != 0;
   // The experts' W_hat^T: dequantized from the saved packed experts, or straight from the
-  // transposing quantizer, or (QF_FLAG_REUSE_WS) transposed from the workspace's W_hat.
+  // transposing quantizer, or (QF_FLAG_REUSE_WS) transposed from the workspace's W_hat, where
+  // every forward leaves one; the experts' amax is in the workspace after any forward.
   const bool from_saved = dX && d->wfmt != QF_FMT_NONE && saved != nullptr;
-  const bool fuse_w = dX && d->wfmt != QF_FMT_NONE && !reuse && !from_saved;
+  const bool fuse_w = dX && d->wfmt != QF_FMT_NONE && !from_saved &&
+                      (!reuse || grouped_decodes_experts(d));
   const uint16_t *Wop, *Aop;
   QF_TRY(grouped_quantize(d, X, W, g, !reuse && dX && !fuse_w && !from_saved, false, &Wop,
                           &Aop, s));
@@ -849,7 +851,8 @@ qf_status qf_qlinear_grouped_bwd_ste(const qf_grouped_desc* d, const int64_t* gr
     } else if (fuse_w) {
       const float* gp = d->w_amax;
       if (d->wfmt == QF_FMT_NVFP4 && !gp) {
-        QF_TRY(dev(qf::launch_amax_batched(W, d->E, d->N, d->K, g.wamax, false, s), "amax"));
+        if (!reuse)
+          QF_TRY(dev(qf::launch_amax_batched(W, d->E, d->N, d->K, g.wamax, false, s), "amax"));
         gp = g.wamax;
       }
       QF_TRY(dev(qf::launch_quant_t(d->wfmt, W, d->N, d->K, d->K, d->E, d->N * d->K, gp, g.whatt,

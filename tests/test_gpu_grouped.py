@@ -96,6 +96,45 @@ def test_grouped_few_rows_per_expert(qf, wfmt, N, K):
         assert_close(dW[e].astype(np.float64), oracle.linear_dw(dY[r0:r1], X[r0:r1]), f"dW e={e}")
 
 
+@pytest.mark.parametrize("wfmt,given", [("nvfp4", False), ("nvfp4", True), ("mxfp4", False),
+                                        ("q4k", False)])
+@pytest.mark.parametrize("rows", [30, 200])
+def test_grouped_kept_workspace_after_a_forward_with_saved(qf, wfmt, given, rows):
+    """A backward with QF_FLAG_REUSE_WS and no saved buffer, after forwards that had one, with the
+    flag in their own descriptor or not: the gradients of the backward from the saved buffer, bit
+    for bit, also where the forward decodes the packed experts (few rows) and writes no W_hat.
+    The workspace starts out as NaNs."""
+    rng = np.random.default_rng(rows)
+    E, N, K = 4, 136, 256
+    offsets = np.array([0, 0, rows, 3 * rows, 4 * rows])
+    T = 4 * rows
+    X, dY = workloads.normal_bf16(rng, (T, K)), workloads.normal_bf16(rng, (T, N))
+    W = np.concatenate([workloads.normal_bf16(rng, (N, K), 0.02 * (e + 1)) for e in range(E)])
+    g = None
+    if given:
+        g = torch.tensor([0.5, 0.25, 1.0, 0.75], dtype=torch.float32, device="cuda")
+    off = torch.from_numpy(offsets.astype(np.int64)).cuda()
+    Xd, Wd, dYd = to_dev(X), to_dev(W), to_dev(dY)
+    outs = []
+    for fflags, from_saved in ((0, True), (0, False), (qf.FLAG_REUSE_WS, False)):
+        d = qf.grouped_desc(E, T, N, K, wfmt, "none", w_amax=g, flags=fflags)
+        ws = qf.grouped_workspace(d)
+        ws.fill_(0xFF)
+        sv = qf.grouped_saved_buffer(d)
+        Y, dX = empty_bf16((T, N)), empty_bf16((T, K))
+        dW = torch.full((E, N, K), 7.0, dtype=torch.float32, device="cuda")
+        qf.qlinear_grouped_fwd(d, off, Xd, Wd, Y, ws, saved=sv)
+        d = qf.grouped_desc(E, T, N, K, wfmt, "none", w_amax=g,
+                            flags=0 if from_saved else qf.FLAG_REUSE_WS)
+        qf.qlinear_grouped_bwd_ste(d, off, dYd, Xd, Wd, dX, dW, ws,
+                                   saved=sv if from_saved else None)
+        torch.cuda.synchronize()
+        outs.append((from_dev(Y), from_dev(dX), from_dev(dW).view(np.uint32)))
+    for other in outs[1:]:
+        for a, b in zip(outs[0], other):
+            assert np.array_equal(a, b)
+
+
 def test_grouped_dw_tile_grid_split_over_xcds(qf):
     """Per-expert dW grids of 5 x 3 tiles (ragged in both dimensions) are dealt to the 8 XCDs
     in shares of 1 or 2 tiles; every expert's gradient is complete, empty experts are zero."""
