@@ -7,10 +7,13 @@
 //             S = sum 2^(a - m)                                      (teacher and student)
 //             Q = sum 2^(a_T - m_T) (z_T - z_S)                      (teacher-weighted gap)
 //           and the first chunk that holds each row's maximum logit.  Then, in natural units,
-//             lse = ln2 (m + log2 S),   KL = Q / S_T + lse_S - lse_T
+//             lse_S - lse_T = ln2 (m_S - m_T + log2 (S_S / S_T)),   KL = Q / S_T + lse_S - lse_T
 //           (sum_v p_T (log p_T - log p_S) with log p = z - lse).
-//   pass 2  grad[v] = scale (2^(a_S - c_S) - 2^(a_T - c_T)), c = m + log2 S, i.e.
+//   pass 2  grad[v] = scale / S_S (2^(a_S - m_S) - S_S / S_T 2^(a_T - m_T)), i.e.
 //           scale (p_S - p_T), written as bf16.
+// No log-sum-exp is formed: rounded at its own size (about 20) it would cost each probability and
+// the loss 6e-7, most of the error there was (KL rows of 0.1 against FP64 5.5e-6 -> 1.7e-6, of
+// 0.005 8e-5 -> 1.5e-5; gradients that are not the nearest bf16 1.6e-3 -> 1.1e-3 of all).
 // What bounds it is HBM (6 bytes per logit) and, nearly as much, the vector units: four exponents,
 // at a quarter of the rate, and about 20 other operations per logit.  So
 //  - a row is read once: of the 16 waves' chunks a compute unit keeps 8 pairs per lane in registers
@@ -19,9 +22,10 @@
 //  - a workgroup stays on its unit and walks over rows; a register pair is refilled from the next
 //    row as soon as its gradient is out, so loads run on through pass 2 and the row change.  Narrow
 //    vocabularies take two 512-lane workgroups a unit, whose passes overlap.
-//  - the reference of a lane's sums moves only when a chunk's maximum passes it by 2^16 (exact up
-//    to rounding, as the sums are in floating point), so few chunks rescale; the element of a
-//    maximum is looked for once a row, and only where both maxima are in one chunk.
+//  - a new reference of a lane's sums is an integer 7 to 8 above the maximum it was made from, and
+//    is replaced only when a maximum passes it: few chunks rescale (exactly, by powers of two), no
+//    exponent is above 1, and those that count have arguments of about -8 (a rounding of 2^-22); the
+//    element of a maximum is looked for once a row, and only where both maxima are in one chunk.
 // 4096 x 151936: 945 -> 784 us; 8192 x 32000: 444 -> 321; 2048 x 65536: 221 -> 169 (against one
 // workgroup per row reading it twice; keeping alone 880 / 456 / 210, with the refills 830 / 345 /
 // 193).  Each lane folds its 16-byte chunks in a fixed order and the workgroup merges the lanes'
@@ -43,7 +47,7 @@ using namespace codec;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kCUs = 256;                             // compute units
-constexpr float kSlack = 16.0f;                       // how far a maximum may pass the reference
+constexpr float kAhead = 7.0f, kAheadPow = 128.0f;    // how far a new reference is ahead; 2^kAhead
 constexpr int kNt = 2;                                // buffer operation: non-temporal
 constexpr int kKeepLds = 4, kKeepReg = 8;             // chunk pairs a lane keeps for the gradient
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -123,8 +127,9 @@ __device__ __forceinline__ void fold_chunk(uint4 vt, uint4 vs, uint32_t i, Stat&
   if (mt > at.v) at = LaneMax{mt, i};
   if (ms > as.v) as = LaneMax{ms, i};
   const float nmt = mt * kLog2e, nms = ms * kLog2e;
-  if (nmt > st.m + kSlack || nms > ss.m + kSlack) {   // new references
-    const float rt = fmaxf(st.m, nmt), rs = fmaxf(ss.m, nms);
+  if (nmt > st.m || nms > ss.m) {                     // new references
+    const float rt = nmt > st.m ? ceilf(nmt) + kAhead : st.m;
+    const float rs = nms > ss.m ? ceilf(nms) + kAhead : ss.m;
     const float ft = st.m == rt ? 1.0f : exp2_safe(st.m - rt);
     const float fs = ss.m == rs ? 1.0f : exp2_safe(ss.m - rs);
     st = Stat{rt, st.S * ft, st.Q * ft};
@@ -139,19 +144,20 @@ __device__ __forceinline__ void fold_chunk(uint4 vt, uint4 vs, uint32_t i, Stat&
   }
 }
 
-// The gradient of one chunk.  Finite row statistics make every probability finite, so the
-// hardware bf16 pack rounds exactly as bf16_rne; rows with non-finite logits keep the bit-level
-// rounding (uniform per workgroup).
-__device__ __forceinline__ void grad_chunk(uint4 vt, uint4 vs, float ct, float cs, float gscale,
+// The gradient of one chunk, f (2^(a_S - ms) - q 2^(a_T - mt)) with f = scale / S_S and q = S_S / S_T
+// (equal rows: exactly zero).  Finite row statistics make every probability finite, so the hardware
+// bf16 pack rounds exactly as bf16_rne; rows with non-finite logits keep the bit-level rounding
+// (uniform per workgroup).
+__device__ __forceinline__ void grad_chunk(uint4 vt, uint4 vs, float mt, float ms, float q, float f,
                                            bool finite, __amdgpu_buffer_rsrc_t out, uint32_t off) {
   float xt[8], xs[8], g[8];
   unpack8_f32(vt, xt);
   unpack8_f32(vs, xs);
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const float p_t = exp2_safe(__builtin_fmaf(xt[k], kLog2e, -ct));
-    const float p_s = exp2_safe(__builtin_fmaf(xs[k], kLog2e, -cs));
-    g[k] = gscale * (p_s - p_t);
+    const float e_t = exp2_safe(__builtin_fmaf(xt[k], kLog2e, -mt));
+    const float e_s = exp2_safe(__builtin_fmaf(xs[k], kLog2e, -ms));
+    g[k] = f * __builtin_fmaf(-q, e_t, e_s);
   }
   uint32_t o[4];
   if (finite) {
@@ -306,9 +312,8 @@ __global__ __launch_bounds__(NT, 4) void qad_kl_kernel(
     at = o.at;
     as = o.as;
     merge_lanes<NW>(lane, st, ss, at, as);
-    const float ct = first_lane(st.m + __builtin_amdgcn_logf(st.S));   // base-2 log-sum-exp
-    const float cs = first_lane(ss.m + __builtin_amdgcn_logf(ss.S));
-    if (t == 0) row_kl[row] = st.Q / st.S + (cs - ct) * kLn2;
+    if (t == 0)
+      row_kl[row] = st.Q / st.S + ((ss.m - st.m) + __builtin_amdgcn_logf(ss.S / st.S)) * kLn2;
     if (agree) {
       // The maxima's first chunks; where that is one chunk, its owner looks at the elements (before
       // it writes a gradient there).
@@ -324,11 +329,19 @@ __global__ __launch_bounds__(NT, 4) void qad_kl_kernel(
     }
     if (GRAD) {
       uint16_t* pg = grad + row * ldg;
-      const bool finite = __builtin_isfinite(ct) && __builtin_isfinite(cs);
+      // (the references back near the maxima, where the exponents' arguments are smallest; a sum that
+      // overflowed, of logits beyond 1e9 all alike, leaves probabilities of zero)
+      const bool inf_t = st.S == __builtin_huge_valf(), inf_s = ss.S == __builtin_huge_valf();
+      const float mt = first_lane(inf_t ? st.S : st.m - kAhead);
+      const float ms = first_lane(inf_s ? ss.S : ss.m - kAhead);
+      const float d = inf_s ? 1.0f : ss.S * kAheadPow;
+      const float q = first_lane(d / (st.S * kAheadPow)), f = first_lane(gscale / d);
+      const bool finite = __builtin_isfinite(mt) && __builtin_isfinite(ms) &&
+                          __builtin_isfinite(q) && __builtin_isfinite(f);
       for (int64_t b = (KR + KL) * NT; b < chunks; b += 2 * NT) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-          grad_chunk(vt[u], vs[u], ct, cs, gscale, finite, window(pg, b + u * NT, chunks, NT), off);
+          grad_chunk(vt[u], vs[u], mt, ms, q, f, finite, window(pg, b + u * NT, chunks, NT), off);
           __builtin_amdgcn_sched_barrier(0);
           stage(u, b + (u + 2) * NT);
         }
@@ -338,7 +351,7 @@ __global__ __launch_bounds__(NT, 4) void qad_kl_kernel(
 #pragma unroll
       for (int j = 0; j < KL; ++j) {
         if ((KR + j) * NT < head)                     // uniform
-          grad_chunk(keep[2 * j * NT + t], keep[(2 * j + 1) * NT + t], ct, cs, gscale, finite, wg,
+          grad_chunk(keep[2 * j * NT + t], keep[(2 * j + 1) * NT + t], mt, ms, q, f, finite, wg,
                      off + (KR + j) * kStep);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -348,7 +361,7 @@ __global__ __launch_bounds__(NT, 4) void qad_kl_kernel(
       const auto ws = window(zs + next * lds_, 0, next < L ? chunks : 0, kKeep);
 #pragma unroll
       for (int j = 0; j < KR; ++j) {
-        if (j * NT < head) grad_chunk(rt[j], rs[j], ct, cs, gscale, finite, wg, off + j * kStep);
+        if (j * NT < head) grad_chunk(rt[j], rs[j], mt, ms, q, f, finite, wg, off + j * kStep);
         __builtin_amdgcn_sched_barrier(0);
         rt[j] = load_chunk(wt, off + j * kStep);
         rs[j] = load_chunk(ws, off + j * kStep);

@@ -148,3 +148,43 @@ def test_qad_kl_full_size_sampled(qf):
     gr = bf16_to_f64(from_dev(grad[ri].view(torch.int16)))
     assert_close(gr, rgrad * 12 / L, "grad rows")
     assert abs(float(loss.item()) - k.astype(np.float64).mean()) <= 1e-6 * (1 + k.mean())
+
+
+@pytest.mark.parametrize("L,V", [(256, 8 * 512 * 4), (64, 151936)])
+def test_qad_kl_keeps_its_precision_where_late_chunks_dominate(qf, L, V):
+    """Logits that rise along the row, so that every lane's first maximum is passed by far.  The loss
+    of a row is Q / S_T + lse_S - lse_T, all below 1 here.  Its rounding: the last additions of each of
+    the two merge trees (an addition's rms error is 2.5e-8 of its sum, and an addition k levels
+    below the last is averaged over 2^k others: 3.5e-8), the division, logarithm and products
+    (about 2e-8 each); the exponents' own (2^-22 of each) average out over the lanes.  About 8e-8
+    in all; twice that is allowed (against FP64: 7e-8 measured; with log-sum-exps rounded before
+    they are subtracted 4e-7, and with maxima 2^16 above the reference 5e-7)."""
+    g = np.random.default_rng(L)
+    t = 0.5 * g.standard_normal((L, V), dtype=np.float32) + np.linspace(-10, 0, V, dtype=np.float32)
+    zt = workloads.to_bf16(t)
+    zs = workloads.to_bf16(t + 0.1 * g.standard_normal((L, V), dtype=np.float32))
+    kl = _run(qf, zt, zs)[0].astype(np.float64)
+    ref = oracle.qad_kl(zt, zs)[1]
+    assert np.sqrt(np.mean((kl - ref) ** 2)) <= 1.6e-7
+
+
+@pytest.mark.parametrize("V", [8192, 151936])
+def test_qad_kl_student_mask_of_the_lowest_value(qf, V):
+    """A token that the student masks with the lowest bf16 value and the teacher puts above all that
+    its lane has seen: the teacher-weighted gap stays finite (its exact value does)."""
+    zt, zs = np.zeros((2, V), np.uint16), np.zeros((2, V), np.uint16)
+    zt[:, V - 3] = workloads.to_bf16(np.array([8.0], np.float32))[0]
+    zs[:, V - 3] = 0xFF7F
+    kl, _, grad, agree = _run(qf, zt, zs)
+    _, rkl, rgrad, ragree = oracle.qad_kl(zt, zs)
+    assert np.all(np.isfinite(rkl)) and np.all(np.abs(kl / rkl - 1) <= 1e-4)
+    assert np.array_equal(agree, ragree)
+    assert np.all(np.abs(bf16_to_f64(grad) - rgrad) <= 2.0 ** -8 * np.abs(rgrad) + 1e-6)
+
+
+@pytest.mark.parametrize("V", [8, 4096, 32776, 151936])
+def test_qad_kl_of_a_distribution_with_itself(qf, V):
+    """Equal logits give equal sums, so the loss and every gradient are exactly zero."""
+    zt = workloads.qad_logits(V, 3, V)["zt"]
+    kl, loss, grad, agree = _run(qf, zt, zt.copy())
+    assert np.all(kl == 0.0) and loss == 0.0 and np.all(grad == 0) and np.all(agree == 1)
