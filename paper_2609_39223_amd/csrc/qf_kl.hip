@@ -227,7 +227,8 @@ __global__ __launch_bounds__(NT, 4) void qad_kl_kernel(
   constexpr int KR = GRAD ? kKeepReg : 0, KL = GRAD ? kKeepLds : 0;
   __shared__ uint4 keep[KL ? KL * 2 * NT : 1];
   __shared__ WaveStat part[2][NW];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int64_t chunks = V >> 3;
 
   // Lane t owns chunks t, t + NT, t + 2 NT, ... of a row: the first KR pairs stay in registers,
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(NT, 4) void qad_kl_kernel(
   int par = 0;
   for (int64_t row = blockIdx.x; row < L; row += gridDim.x, par ^= 1) {
     // opaque: conditions and offsets of the unrolled parts are not carried in registers
-    asm volatile("" : "+s"(head), "+v"(off));
+    if (GRAD) asm volatile("" : "+s"(head), "+v"(off));
     const uint16_t* pt = zt + row * ldt;
     const uint16_t* ps = zs + row * lds_;
     Stat st{-__builtin_huge_valf(), 0.0f, 0.0f};
@@ -306,6 +307,7 @@ __global__ __launch_bounds__(NT, 4) void qad_kl_kernel(
       part[par][wv] = WaveStat{st, ss, at, as};
     }
     __syncthreads();
+    if (!GRAD && wv) break;                           // (one row a workgroup, its first wave ends it)
     const WaveStat& o = part[par][lane < NW ? lane : 0];
     st = o.st;
     ss = o.ss;
@@ -320,7 +322,7 @@ __global__ __launch_bounds__(NT, 4) void qad_kl_kernel(
       const int64_t it = first_lane(at.i), is = first_lane(as.i);
       if (it != is || it >= chunks) {
         if (t == 0) agree[row] = it == is ? 1 : 0;
-      } else if (t == (int)(it & (NT - 1))) {
+      } else if (t == (GRAD ? (int)(it & (NT - 1)) : 0)) {
         float xt[8], xs[8];
         unpack8_f32(*reinterpret_cast<const uint4*>(pt + it * 8), xt);
         unpack8_f32(*reinterpret_cast<const uint4*>(ps + it * 8), xs);
@@ -401,14 +403,17 @@ hipError_t launch_qad_kl(const uint16_t* zt, int64_t ldt, const uint16_t* zs, in
   if (L > 0) {
     // Two 512-lane workgroups a unit where they keep most of a row (against one of 1024, us: 8192 x
     // 32000 328 / 416, 2048 x 49152 127 / 148, 2048 x 65536 169 / 182, 2048 x 100000 272 / 273, 4096 x
-    // 151936 863 / 797).
+    // 151936 863 / 797).  The same with fewer rows than units, where a unit has one of them: 16 x
+    // 16384 12.5 / 14.5, 64 x 32000 15.0 / 17.0, 256 x 32000 17.5 / 18.7, 64 x 65536 21.8 / 22.3; and
+    // without a gradient, where all four that fit run (the row kernel of one 1024-lane workgroup and
+    // a merge by one lane: 1024 x 4096 23.1, 1024 x 32000 43.3, 256 x 32000 15.0): 1024 x 4096 14.6 /
+    // 24.7, 1024 x 32000 32.3 / 41.2, 256 x 32000 12.5 / 13.4, 64 x 65536 15.8 / 15.2.
     const bool wide = V > 65536;
-    auto* k = !grad ? &qad_kl_kernel<1024, false>
-              : wide ? &qad_kl_kernel<1024, true> : &qad_kl_kernel<512, true>;
+    auto* k = wide ? (grad ? &qad_kl_kernel<1024, true> : &qad_kl_kernel<1024, false>)
+                   : (grad ? &qad_kl_kernel<512, true> : &qad_kl_kernel<512, false>);
     const int64_t slots = wide ? kCUs : 2 * kCUs;
-    hipLaunchKernelGGL(k, dim3((unsigned)(grad && L > slots ? slots : L)),
-                       dim3(grad && !wide ? 512 : 1024), 0, s, zt, ldt, zs, lds_, L, V, gscale,
-                       row_kl, grad, ldg, agree);
+    hipLaunchKernelGGL(k, dim3((unsigned)(grad && L > slots ? slots : L)), dim3(wide ? 1024 : 512), 0,
+                       s, zt, ldt, zs, lds_, L, V, gscale, row_kl, grad, ldg, agree);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

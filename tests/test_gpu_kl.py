@@ -188,3 +188,14 @@ def test_qad_kl_of_a_distribution_with_itself(qf, V):
     zt = workloads.qad_logits(V, 3, V)["zt"]
     kl, loss, grad, agree = _run(qf, zt, zt.copy())
     assert np.all(kl == 0.0) and loss == 0.0 and np.all(grad == 0) and np.all(agree == 1)
+
+
+@pytest.mark.parametrize("V", [520, 12296, 32000, 65536, 65544])
+def test_qad_kl_same_loss_with_and_without_gradient(qf, V):
+    """The loss rows and the agreement do not depend on whether the gradient is asked for: both
+    launches deal a row to as many lanes."""
+    d = workloads.qad_logits(V + 1, 9, V)
+    a = _run(qf, d["zt"], d["zs"], with_grad=True)
+    b = _run(qf, d["zt"], d["zs"], with_grad=False)
+    assert np.array_equal(a[0], b[0]) and a[1] == b[1] and np.array_equal(a[3], b[3])
+    _check(b, oracle.qad_kl(d["zt"], d["zs"]), f"V={V}")
