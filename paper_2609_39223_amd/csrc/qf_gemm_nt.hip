@@ -899,16 +899,6 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(NtArgs p) {
   }
 }
 
-// Blocks resident at once: one block per CU (its LDS).
-int64_t resident_blocks() {
-  int dev = 0, ncu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      ncu <= 0)
-    return 256;
-  return ncu;
-}
-
 // The loads address a tile with 32-bit byte offsets from its first element: a k-major operand
 // spans 256 rows, an mn-major one all K rows.
 bool nt_offsets_fit(int64_t K, int64_t lda, int64_t ldb, bool a_mn = false, bool b_mn = false) {
@@ -922,6 +912,15 @@ int vec_store_ok(const void* C, int64_t ldc, int esize) {
 }
 
 }  // namespace
+
+int64_t compute_units() {
+  int dev = 0, ncu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      ncu <= 0)
+    return 256;
+  return ncu;
+}
 
 // With few rows per expert half of a 256-row tile is padding.  The grouped layer's forward +
 // backward (NVFP4, saved operands; E x rows per expert, N x K), us, in 256- / 128-row tiles: 64 x 16,
@@ -957,7 +956,7 @@ GemmTile gemm_tile(int64_t M, int64_t N, bool halves = false) {
       {GemmTile::k128x128, 128, 128}, {GemmTile::k128x64, 128, 64},
       {GemmTile::k64x64, 64, 64},     {GemmTile::k32x32, 32, 32},
       {GemmTile::k16x16, 16, 16}};
-  const int64_t cus = resident_blocks();
+  const int64_t cus = compute_units();
   GemmTile best = GemmTile::k256x256;
   int64_t cost = INT64_MAX;
   for (const auto& c : kTiles) {
@@ -997,7 +996,7 @@ hipError_t launch_dense(int64_t M, int64_t N, int64_t K, const uint16_t* A, int6
   // A last round of 256 x 256 tiles that would leave at least half the CUs idle runs as K-halves
   // instead (FP32 output only; needs a partial buffer and at least two full stages).  The split is
   // decided per XCD: each runs tiles / 8 tiles on cus / 8 CUs.
-  const int64_t cus = resident_blocks();
+  const int64_t cus = compute_units();
   const int64_t t256 = ((M + BM - 1) / BM) * ((N + BN - 1) / BN), rem = t256 % cus;
   const bool halves = c_f32 && part != nullptr && t256 % kXcds == 0 && cus % kXcds == 0 &&
                       rem > 0 && 2 * rem <= cus && rem <= kMaxSplitTiles && K / BK >= 2;

@@ -72,6 +72,10 @@ hipError_t launch_quant_t_grouped(int fmt, const uint16_t* x, int64_t T, int64_t
                                   const int64_t* off, const int* kstart, int64_t E,
                                   uint16_t* out, int64_t ldo, hipStream_t s);
 
+// Compute units of the current device (256 where it cannot be asked): the workgroups that run at
+// once where one fills a unit's LDS or registers.
+int64_t compute_units();
+
 // ---- GEMMs --------------------------------------------------------------------------------
 // NT GEMM (qf_gemm_nt.hip): C[m, n] = sum_k A(m, k) B(n, k).  A is [M][K] (k contiguous) or,
 // with a_mn, [K][M] (m contiguous); likewise B [N][K] or [K][N] with b_mn.  Row strides and

@@ -46,7 +46,6 @@ using namespace codec;
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr int kCUs = 256;                             // compute units
 constexpr float kAhead = 7.0f, kAheadPow = 128.0f;    // how far a new reference is ahead; 2^kAhead
 constexpr int kNt = 2;                                // buffer operation: non-temporal
 constexpr int kKeepLds = 4, kKeepReg = 8;             // chunk pairs a lane keeps for the gradient
@@ -411,7 +410,7 @@ hipError_t launch_qad_kl(const uint16_t* zt, int64_t ldt, const uint16_t* zs, in
     const bool wide = V > 65536;
     auto* k = wide ? (grad ? &qad_kl_kernel<1024, true> : &qad_kl_kernel<1024, false>)
                    : (grad ? &qad_kl_kernel<512, true> : &qad_kl_kernel<512, false>);
-    const int64_t slots = wide ? kCUs : 2 * kCUs;
+    const int64_t slots = (wide ? 1 : 2) * compute_units();
     hipLaunchKernelGGL(k, dim3((unsigned)(grad && L > slots ? slots : L)), dim3(wide ? 1024 : 512), 0,
                        s, zt, ldt, zs, lds_, L, V, gscale, row_kl, grad, ldg, agree);
     const hipError_t e = hipGetLastError();
