@@ -646,7 +646,7 @@ qf_status qf_qlinear_bwd_ste(const qf_qlinear_desc* d, const uint16_t* dY, const
 namespace {
 
 struct GroupedWs {
-  int* tile_start;  // [E+1]
+  int* tile_start;  // [E+2]
   int* order;       // [E]
   float* wamax;     // [E]
   uint16_t* what;   // [E, N, K]
@@ -662,7 +662,7 @@ struct GroupedWs {
 int64_t grouped_tpad(const qf_grouped_desc* d) { return (d->T + 63 * d->E + 63) / 64 * 64; }
 
 size_t grouped_ws_bytes(const qf_grouped_desc* d) {
-  size_t b = up((size_t)(d->E + 1) * 4) + up((size_t)d->E * 4) + up((size_t)d->E * 4);
+  size_t b = up((size_t)(d->E + 2) * 4) + up((size_t)d->E * 4) + up((size_t)d->E * 4);
   if (d->wfmt != QF_FMT_NONE) b += up((size_t)d->E * d->N * d->K * 2);
   if (d->afmt != QF_FMT_NONE) b += up((size_t)d->T * d->K * 2);
   b += up((size_t)d->E * d->N * d->K * 2);
@@ -675,7 +675,7 @@ size_t grouped_ws_bytes(const qf_grouped_desc* d) {
 GroupedWs grouped_ws(const qf_grouped_desc* d, void* ws) {
   char* p = static_cast<char*>(ws);
   GroupedWs g{};
-  g.tile_start = reinterpret_cast<int*>(p); p += up((size_t)(d->E + 1) * 4);
+  g.tile_start = reinterpret_cast<int*>(p); p += up((size_t)(d->E + 2) * 4);
   g.order = reinterpret_cast<int*>(p); p += up((size_t)d->E * 4);
   g.wamax = reinterpret_cast<float*>(p); p += up((size_t)d->E * 4);
   if (d->wfmt != QF_FMT_NONE) { g.what = reinterpret_cast<uint16_t*>(p); p += up((size_t)d->E * d->N * d->K * 2); }
@@ -792,7 +792,8 @@ qf_status qf_qlinear_grouped_fwd(const qf_grouped_desc* d, const int64_t* group_
   const Packed pk = saved ? grouped_saved_layout(d, saved) : Packed{};
   const bool fused = saved != nullptr && grouped_decodes_experts(d);
   QF_TRY(grouped_quantize(d, X, W, g, true, true, &Wop, &Aop, s, saved ? &pk : nullptr, fused));
-  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, qf::grouped_tile_rows(d->E, d->T),
+  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E,
+                                     fused ? 128 : qf::grouped_tile_rows(d->E, d->T), d->N,
                                      g.tile_start, g.order, g.kstart, s),
              "prep"));
   if (fused) {
@@ -833,11 +834,11 @@ qf_status qf_qlinear_grouped_bwd_ste(const qf_grouped_desc* d, const int64_t* gr
   const uint16_t *Wop, *Aop;
   QF_TRY(grouped_quantize(d, X, W, g, !reuse && dX && !fuse_w && !from_saved, false, &Wop,
                           &Aop, s));
-  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, qf::grouped_tile_rows(d->E, d->T),
+  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, qf::grouped_tile_rows(d->E, d->T), d->K,
                                      g.tile_start, g.order, g.kstart, s),
              "prep"));
   // dY^T in the padded layout of dW is written by the dX launch from the dY tiles it stages
-  // when both gradients are asked for, its tiles have 256 rows and it spans at least 8 tile columns
+  // when both gradients are asked for, its tiles surely have 256 rows and it spans at least 8 tile columns
   // (K >= 1793); otherwise by the grouped transposer
   const int64_t tp = grouped_tpad(d), ldt = ws_ld(tp);
   const bool dyt_by_dx = dX != nullptr && dW != nullptr && (d->K + 255) / 256 >= 8 &&
@@ -1246,7 +1247,7 @@ qf_status qf_qlinear_lora_bwd_ste(const qf_qlinear_desc* d, const qf_lora* lora,
 namespace {
 
 // Workspace of the grouped LoRA layer (256-byte aligned regions):
-//   tile_start, order  [E+1], [E]   grouped NT row tiles (launch_grouped_prep)
+//   tile_start, order  [E+2], [E]   grouped NT row tiles (launch_grouped_prep)
 //   pre16, prech       [E+1] x 2    row-dot / column-sum chunk prefixes
 //   wamax              [E]          per-expert merged amax (NVFP4)
 //   what               [E, N, K]    per-expert W_hat of the merged weights
@@ -1273,7 +1274,7 @@ struct GroupedLoraWs {
 size_t glora_ws_bytes(const qf_grouped_desc* d, int64_t r, int b_shared) {
   const size_t E = d->E, T = d->T, N = d->N, K = d->K, R = r, RP = (R + 15) / 16 * 16;
   const size_t Eb = b_shared ? 1 : E;
-  size_t b = up((E + 1) * 4) + up(E * 4) + 2 * up((E + 1) * 4) + up(E * 4);
+  size_t b = up((E + 2) * 4) + up(E * 4) + 2 * up((E + 1) * 4) + up(E * 4);
   b += up(E * N * K * 2);
   if (d->afmt != QF_FMT_NONE) b += up(T * K * 2);
   b += up(E * K * N * 2) + up(Eb * R * N * 4) + 2 * up(T * RP * 4);
@@ -1287,7 +1288,7 @@ GroupedLoraWs glora_ws(const qf_grouped_desc* d, int64_t r, int b_shared, void* 
   const size_t Eb = b_shared ? 1 : E;
   char* p = static_cast<char*>(ws);
   GroupedLoraWs g{};
-  g.tile_start = reinterpret_cast<int*>(p); p += up((E + 1) * 4);
+  g.tile_start = reinterpret_cast<int*>(p); p += up((E + 2) * 4);
   g.order = reinterpret_cast<int*>(p); p += up(E * 4);
   g.pre16 = reinterpret_cast<int*>(p); p += up((E + 1) * 4);
   g.prech = reinterpret_cast<int*>(p); p += up((E + 1) * 4);
@@ -1388,7 +1389,7 @@ qf_status qf_qlinear_grouped_lora_fwd(const qf_grouped_desc* d, const qf_lora* l
     QF_TRY(dev(qf::launch_mxfp4(X, d->T, d->K, d->K, nullptr, nullptr, g.ahat, s), "mxfp4"));
     Aop = g.ahat;
   }
-  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, qf::grouped_tile_rows(d->E, d->T),
+  QF_TRY(dev(qf::launch_grouped_prep(group_offsets, d->E, qf::grouped_tile_rows(d->E, d->T), d->N,
                                      g.tile_start, g.order, nullptr, s),
              "prep"));
   QF_TRY(dev(qf::launch_grouped_nt_rows(d->E, d->T, d->N, d->K, group_offsets, g.tile_start, Aop,
@@ -1419,7 +1420,7 @@ qf_status qf_qlinear_grouped_lora_bwd_ste(const qf_grouped_desc* d, const qf_lor
   const bool reuse = (d->flags & QF_FLAG_REUSE_WS) != 0;
   const int64_t E = d->E, T = d->T, N = d->N, K = d->K, r = lora->r, rp = (r + 15) / 16 * 16;
   if (dX) {
-    QF_TRY(dev(qf::launch_grouped_prep(group_offsets, E, qf::grouped_tile_rows(E, T), g.tile_start,
+    QF_TRY(dev(qf::launch_grouped_prep(group_offsets, E, qf::grouped_tile_rows(E, T), K, g.tile_start,
                                        g.order, nullptr, s),
                "prep"));
     if (reuse) {

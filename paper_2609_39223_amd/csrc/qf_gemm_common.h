@@ -42,7 +42,7 @@ struct NtArgs {
   int64_t M, N, K;
   int tiles_m, tiles_n;
   const int64_t* off;     // grouped rows: [E+1] row offsets
-  const int* tile_start;  // grouped rows: [E+1] per-expert tile prefix
+  const int* tile_start;  // grouped rows: [E+1] per-expert tile prefix, then the rows of a tile
   int E;
   // grouped K (per-expert weight gradient): expert e contracts over k in
   // [BK kstart[e], BK kstart[e+1]) and writes C + e cstride; order[] lists experts by

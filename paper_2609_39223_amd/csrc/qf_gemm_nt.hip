@@ -85,6 +85,14 @@ __device__ __forceinline__ void acc_settle(f32x4_t (&acc)[TM][TN]) {
   if (BEGIN) asm volatile("s_nop 7");
 }
 
+// A value that all lanes share, in scalar registers (loaded through a pointer, the compiler may keep
+// it in vector registers, and then wraps every buffer operation whose resource depends on it in a
+// loop over the lanes' values).
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+  return ((int64_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | lo;
+}
+
 // f(0), f(1), .. f(N - 1) with compile-time indices (std::integral_constant arguments)
 template <class F, int... I>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
@@ -93,6 +101,12 @@ __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// LDS bytes of a tile: two stages (and the prefetches' landing place), or its bf16 form padded
+constexpr int nt_smem_bytes(int TM, int TN, bool PF) {
+  const int stages = 2 * 32 * (TM + TN) * kRow + (PF ? 1024 : 0), c16 = 32 * TM * (64 * TN + 16);
+  return stages > c16 ? stages : c16;
 }
 
 // TM x TN: 16 x 16 accumulator blocks of a wavefront's sub-tile; the 2 x 2 wavefronts of a
@@ -118,9 +132,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 //
 // AT2 (A^T modes): a tile may own two A^T pieces per stage (fewer than 16 tile columns); without
 // it the launch has at least 16 and a tile owns at most one.
-template <bool C_F32, int MODE, int TM, int TN, int BQ = 0, bool BF = false, bool AT2 = false,
-          bool PF = false>
-__global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
+template <bool C_F32, int MODE, int TM, int TN, int BQ, bool BF, bool AT2, bool PF>
+__device__ __forceinline__ void gemm_nt_tile(const NtArgs& p, char* smem) {
   static_assert((TM == 8 && (TN == 8 || TN == 4)) || (TM == 4 && TN == 8 && MODE == kGroupRows),
                 "256-row tiles of 256 or 128 columns; per expert also 128 rows by 256 columns");
   static_assert(BQ == 0 || (TN == 8 && (MODE == kDense || MODE == kGroupRows) && !C_F32),
@@ -132,13 +145,11 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
   constexpr int kStage = (BM + BN) * kRow;
   constexpr int kPitch16 = BN * 2 + 16;          // epilogue LDS row pitch, bf16 tile
   constexpr int kPitch32 = BN * 4 + 16;          // epilogue LDS row pitch, FP32 half tile
-  constexpr int kMain = 2 * kStage + (PF ? 1024 : 0);   // (the prefetches' landing place)
-  constexpr int kSmem = kMain > BM * kPitch16 ? kMain : BM * kPitch16;
+  constexpr int kSmem = nt_smem_bytes(TM, TN, PF);
   static_assert(BM / 2 * kPitch32 <= kSmem, "the FP32 half tile fits the stages' LDS");
   // direct-to-LDS loads per wavefront per stage: TM of A, then TN of B (packed or
   // fragment-major B: A's only)
   constexpr int NLD = (BQ != 0 || BF) ? TM : TM + TN;
-  __shared__ __attribute__((aligned(16))) char smem[kSmem];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform (scalar) index
@@ -196,7 +207,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
     // tile_start[E].  Block b runs on XCD x = b % 8 as its item j = b / 8, and XCD x takes the
     // contiguous range [x per, (x + 1) per) of the real items (per = ceil(items / 8)), so the
     // XCDs get equal shares and their 32 CUs share the expert weight panels in their L2.
-    const int items = p.tile_start[p.E] * p.tiles_n;
+    const int items = __builtin_amdgcn_readfirstlane(p.tile_start[p.E]) * p.tiles_n;
     const int per = (items + kXcds - 1) / kXcds;
     const int j = blockIdx.x / kXcds, it = (blockIdx.x % kXcds) * per + j;
     if (j >= per || it >= items) return;         // uniform over the block
@@ -206,8 +217,9 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
       const int mid = (lo + hi) >> 1;
       if (p.tile_start[mid] <= mt) lo = mid; else hi = mid;
     }
-    m0 = p.off[lo] + (int64_t)(mt - p.tile_start[lo]) * BM;
-    m_end = p.off[lo + 1];
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    m0 = uniform64(p.off[lo] + (int64_t)(mt - p.tile_start[lo]) * BM);
+    m_end = uniform64(p.off[lo + 1]);
     n0 = (int64_t)tn * BN;
     if (AT) {
       at_col0 = 64 * (int64_t)p.kstart[lo] + (m0 - p.off[lo]);
@@ -876,6 +888,22 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
   }
 }
 
+template <bool C_F32, int MODE, int TM, int TN, int BQ = 0, bool BF = false, bool AT2 = false,
+          bool PF = false>
+__global__ __launch_bounds__(256, 1) void gemm_nt_kernel(NtArgs p) {
+  __shared__ __attribute__((aligned(16))) char smem[nt_smem_bytes(TM, TN, PF)];
+  gemm_nt_tile<C_F32, MODE, TM, TN, BQ, BF, AT2, PF>(p, smem);
+}
+
+// Grouped rows in tiles of 256 or 128 rows, as launch_grouped_prep has chosen.
+__global__ __launch_bounds__(256, 1) void gemm_nt_rows_kernel(NtArgs p) {
+  __shared__ __attribute__((aligned(16))) char smem[nt_smem_bytes(8, 8, true)];
+  if (p.tile_start[p.E + 1] == 128)
+    gemm_nt_tile<false, kGroupRows, 4, 8, 0, false, false, true>(p, smem);
+  else
+    gemm_nt_tile<false, kGroupRows, 8, 8, 0, false, false, true>(p, smem);
+}
+
 // C[tile] = part[2 i] + part[2 i + 1] for the split tiles split_from + i (dense mode, FP32):
 // four consecutive columns per lane.  The two halves are added in a fixed order, so the
 // result does not depend on which half finished first.
@@ -922,11 +950,12 @@ int64_t compute_units() {
   return ncu;
 }
 
-// With few rows per expert half of a 256-row tile is padding.  The grouped layer's forward +
-// backward (NVFP4, saved operands; E x rows per expert, N x K), us, in 256- / 128-row tiles: 64 x 16,
-// 2048 x 2048 1014 / 973, 128 x 64, 3072 x 2048 2961 / 2809, 64 x 96, 2048 x 2048 1065 / 994; no gain
-// from 128 rows per expert on (128 x 128, 3072 x 3072 4632 / 4652, 128 x 187 4854 / 4954).
-int grouped_tile_rows(int64_t E, int64_t T) { return T <= 96 * E ? 128 : 256; }
+// With few rows per expert half of a 256-row tile is padding, and the launch chooses between 256 and
+// 128 rows on the device (grouped_prep_kernel).  The grouped layer's forward + backward (NVFP4, saved
+// operands; E x rows per expert, N x K), us, in 256- / 128-row tiles: 64 x 16, 2048 x 2048 1014 / 973,
+// 128 x 64, 3072 x 2048 2961 / 2809, 64 x 96, 2048 x 2048 1065 / 994; no gain from 128 rows per expert
+// on (128 x 128, 3072 x 3072 4632 / 4652, 128 x 187 4854 / 4954), where dX writes dY^T instead.
+int grouped_tile_rows(int64_t E, int64_t T) { return T <= 96 * E ? 0 : 256; }
 
 size_t gemm_nt_split_bytes(int64_t M, int64_t N) {
   const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
@@ -1153,12 +1182,12 @@ hipError_t launch_grouped_nt_rows(int64_t E, int64_t T, int64_t N, int64_t K, co
   a.at = at; a.ldat = ldat; a.kstart = kstart;
   a.vec_store = vec_store_ok(C, ldc, 2);
   a.tiles_n = (int)((N + BN - 1) / BN);
-  a.tiles_m = (int)((T + rows - 1) / rows + E);
+  a.tiles_m = (int)(rows ? (T + rows - 1) / rows + E : (T + 127) / 128 + E);
   const int64_t per = ((int64_t)a.tiles_m * a.tiles_n + kXcds - 1) / kXcds;
   const dim3 grid((unsigned)(kXcds * per));
   if (at != nullptr && a.tiles_n < 16) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRowsAT, 8, 8, 0, false, true, true>), grid, dim3(256), 0, s, a);
   else if (at != nullptr) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRowsAT, 8, 8, 0, false, false, true>), grid, dim3(256), 0, s, a);
-  else if (rows == 128) hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRows, 4, 8, 0, false, false, true>), grid, dim3(256), 0, s, a);
+  else if (rows == 0) hipLaunchKernelGGL(gemm_nt_rows_kernel, grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((gemm_nt_kernel<false, kGroupRows, 8, 8, 0, false, false, true>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }

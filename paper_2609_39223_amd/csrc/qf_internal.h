@@ -116,10 +116,11 @@ hipError_t launch_grouped_nt_k(int64_t E, int64_t M, int64_t N, int64_t Kpad, co
                                 const int* order, const uint16_t* A, int64_t lda,
                                 const uint16_t* B, int64_t ldb, float* C, int64_t ldc,
                                 int64_t cstride, hipStream_t s);
-// Rows of a tile of the grouped NT launches below, 128 or 256: tile_start counts such tiles.
+// Rows of a tile of launch_grouped_nt_rows: 256, or 0 where launch_grouped_prep chooses 128 or 256 from
+// the experts' row counts.
 int grouped_tile_rows(int64_t E, int64_t T);
 // Grouped NT: rows [off[e], off[e+1]) of A use B + e * bstride ([N][K], k
-// contiguous).  With `at` (256-row tiles, N spanning at least 8 tile columns, kstart
+// contiguous).  With `at` (grouped_tile_rows 256, N spanning at least 8 tile columns, kstart
 // from launch_grouped_prep, ldat a multiple of 4 below kGemmAtMaxLd, at 8-byte aligned) the
 // launch also writes A^T in the padded layout of the grouped weight gradient: row k, column
 // 64 kstart[e] + i holds A[off[e] + i][k], zeros up to 64 kstart[e+1].
@@ -130,8 +131,8 @@ hipError_t launch_grouped_nt_rows(int64_t E, int64_t T, int64_t N, int64_t K, co
                                   uint16_t* at = nullptr, int64_t ldat = 0,
                                   const int* kstart = nullptr);
 // The grouped forward's rows against packed NVFP4 / MXFP4 experts (layout as in
-// launch_gemm_nt_packed_b, the experts' rows back to back, decode scale S[e]), and whether the
-// kernel takes E experts and T rows in all and is the faster form for them.
+// launch_gemm_nt_packed_b, the experts' rows back to back, decode scale S[e]) in 128-row tiles, and
+// whether the kernel takes E experts and T rows in all and is the faster form for them.
 bool grouped_packed_b_ok(int fmt, int64_t E, int64_t T, int64_t K);
 hipError_t launch_grouped_nt_rows_packed_b(int64_t E, int64_t T, int64_t N, int64_t K,
                                            const int64_t* off, const int* tile_start,
@@ -147,9 +148,10 @@ hipError_t launch_transpose_bf16(const uint16_t* in, int64_t R, int64_t C, int64
 
 // Grouped over experts (qf_grouped.hip; rows [off[e], off[e+1]) of the token-major operands belong to
 // expert e; the host never reads off).  launch_grouped_prep fills small device arrays:
-// tile_start[E+1] (prefix of per-expert counts of tile_rows-row tiles), order[E] (experts by
-// decreasing row count) and, when non-null, kstart[E+1] (prefix of per-expert 64-row counts).
-hipError_t launch_grouped_prep(const int64_t* off, int64_t E, int tile_rows, int* tile_start,
+// tile_start[E+2] (prefix of per-expert counts of tile_rows-row tiles, 128 or 256, or 0: chosen for a
+// launch of N output columns; then the rows of a tile), order[E] (experts by decreasing row count)
+// and, when non-null, kstart[E+1] (prefix of per-expert 64-row counts).
+hipError_t launch_grouped_prep(const int64_t* off, int64_t E, int tile_rows, int64_t N, int* tile_start,
                                int* order, int* kstart, hipStream_t s);
 
 // ---- LoRA-QAD (qf_lora.hip) ------------------------------------------------------------------

@@ -96,6 +96,34 @@ def test_grouped_few_rows_per_expert(qf, wfmt, N, K):
         assert_close(dW[e].astype(np.float64), oracle.linear_dw(dY[r0:r1], X[r0:r1]), f"dW e={e}")
 
 
+@pytest.mark.parametrize("E,N,K,big", [
+    (32, 2056, 64, 0),       # 9 tile columns: 288 tiles of either height, two rounds
+    (32, 2048, 64, 130),     # one round of 256-row tiles, two of 128-row ones: 256
+    (32, 2048, 64, 128),     # one round of either: 128
+    (64, 1032, 128, 0), (64, 768, 1544, 300), (65, 40, 64, 70), (1024, 16, 32, 200)])
+def test_grouped_tile_height_chosen_from_the_row_counts(qf, E, N, K, big):
+    """At most 96 rows per expert: the launch takes 128- or 256-row tiles as their rounds on the chip
+    are fewer; up to 1024 experts (16 wavefronts of prefix sums), most of them with few rows and some
+    with none.  Against the oracle."""
+    rng = np.random.default_rng(E + N + big)
+    counts = rng.integers(0, 3, E)
+    counts[[0, E // 2, E - 1]] = [big, 5, 1]
+    counts[E // 3:E // 3 + 3] = big, 0, big // 2
+    offsets = np.concatenate([[0], np.cumsum(counts)])
+    T = int(offsets[-1])
+    X, dY = workloads.normal_bf16(rng, (T, K)), workloads.normal_bf16(rng, (T, N))
+    W = workloads.normal_bf16(rng, (E * N, K), 0.02).reshape(E, N, K)
+    Y, dX, dW = run_grouped(qf, offsets, X, W, dY, "none", "none")
+    for e in range(E):
+        r0, r1 = offsets[e], offsets[e + 1]
+        if r1 == r0:
+            assert np.all(dW[e] == 0.0)
+        elif r1 - r0 > 2 or e % 64 == 0:
+            assert_close(bf16_to_f64(Y[r0:r1]), oracle.linear_fwd(X[r0:r1], W[e]), f"Y e={e}")
+            assert_close(bf16_to_f64(dX[r0:r1]), oracle.linear_dx(dY[r0:r1], W[e]), f"dX e={e}")
+            assert_close(dW[e].astype(np.float64), oracle.linear_dw(dY[r0:r1], X[r0:r1]), f"dW e={e}")
+
+
 @pytest.mark.parametrize("wfmt,given", [("nvfp4", False), ("nvfp4", True), ("mxfp4", False),
                                         ("q4k", False)])
 @pytest.mark.parametrize("rows", [30, 200])
