@@ -716,7 +716,7 @@ qf_status check_grouped(const char* fn, const qf_grouped_desc* d, const int64_t*
 // no W_hat in the workspace: whether there is one depends on an argument that the backward does
 // not see, so a QF_FLAG_REUSE_WS backward of such a layer never takes W_hat from there.
 bool grouped_decodes_experts(const qf_grouped_desc* d) {
-  return qf::grouped_packed_b_ok(d->wfmt, d->E, d->T, d->K);
+  return qf::grouped_packed_b_ok(d->wfmt, d->E, d->T, d->N, d->K);
 }
 
 // W_hat (unless packed_only; with pk, the experts' packed W_hat in the same launch) and A_hat.

@@ -1196,9 +1196,22 @@ hipError_t launch_grouped_nt_rows(int64_t E, int64_t T, int64_t N, int64_t K, co
 // for that.  Forward, us, from W_hat / decoded here (128-row tiles): 64 x 16 rows, 2048 x 2048 NVFP4
 // 443 / 381, MXFP4 345 / 293; 128 x 64, 3072 x 2048 1325 / 1181 and 1042 / 959; 64 x 96, 2048 x 2048
 // 452 / 451 and 362 / 382.  Q4_K's longer decode does not pay (128 x 64: 1126 / 1186).
-bool grouped_packed_b_ok(int fmt, int64_t E, int64_t T, int64_t K) {
-  return (fmt == QF_FMT_NVFP4 || fmt == QF_FMT_MXFP4) && K > 0 && K % BK == 0 && T <= 64 * E &&
-         nt_offsets_fit(K, K, K);
+// Nor does any where a few tiles decode one after another and W_hat comes back out of the 256 MB
+// last-level cache, beside W (NVFP4, us; tiles, W_hat): 8 x 2048 x 2048, 64, 67 MB 71 / 91; 8 x 3072 x
+// 2048, 96, 100 MB 91 / 105; 32 x 1024 x 1536, 128, 100 MB 87 / 96; 16 x 2560 x 1024, 160, 84 MB
+// 70 / 72.  From 128 MB on it pays from 96 tiles on (8 x 3072 x 3072, 151 MB 160 / 143; 16 x 2048 x
+// 2048, 134 MB 133 / 124), and from 192 tiles on throughout (16 x 3072 x 1024, 100 MB 80 / 78).
+// And not where 256-row tiles, in which decoding is slower, may make one round of what 128-row tiles
+// make two of: with a tile for every expert just one round, and rows enough that routing as skewed as
+// Zipf's gives an expert more than 128 of them (32 x 48 rows, 2048 x 2048: 227 / 249; 32 x 16, where
+// it does not: 218 / 193).
+bool grouped_packed_b_ok(int fmt, int64_t E, int64_t T, int64_t N, int64_t K) {
+  if ((fmt != QF_FMT_NVFP4 && fmt != QF_FMT_MXFP4) || K <= 0 || K % BK != 0 || T > 64 * E ||
+      !nt_offsets_fit(K, K, K))
+    return false;
+  const int64_t cols = (N + BN - 1) / BN, tiles = E * cols, cus = compute_units();
+  if (tiles <= cus && (E + T / 1024) * cols > cus) return false;
+  return tiles >= 192 || (tiles >= 96 && E * N * K >= (int64_t)1 << 26);
 }
 
 hipError_t launch_grouped_nt_rows_packed_b(int64_t E, int64_t T, int64_t N, int64_t K,
@@ -1207,7 +1220,7 @@ hipError_t launch_grouped_nt_rows_packed_b(int64_t E, int64_t T, int64_t N, int6
                                            const uint8_t* codes, const uint8_t* scales,
                                            const float* S, uint16_t* C, int64_t ldc,
                                            hipStream_t s) {
-  if (!grouped_packed_b_ok(bfmt, E, T, K) || codes == nullptr || scales == nullptr ||
+  if (!grouped_packed_b_ok(bfmt, E, T, N, K) || codes == nullptr || scales == nullptr ||
       (bfmt == QF_FMT_NVFP4 && S == nullptr))
     return hipErrorInvalidValue;
   if (T == 0 || N == 0 || E == 0) return hipSuccess;

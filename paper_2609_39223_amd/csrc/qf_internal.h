@@ -133,7 +133,7 @@ hipError_t launch_grouped_nt_rows(int64_t E, int64_t T, int64_t N, int64_t K, co
 // The grouped forward's rows against packed NVFP4 / MXFP4 experts (layout as in
 // launch_gemm_nt_packed_b, the experts' rows back to back, decode scale S[e]) in 128-row tiles, and
 // whether the kernel takes E experts and T rows in all and is the faster form for them.
-bool grouped_packed_b_ok(int fmt, int64_t E, int64_t T, int64_t K);
+bool grouped_packed_b_ok(int fmt, int64_t E, int64_t T, int64_t N, int64_t K);
 hipError_t launch_grouped_nt_rows_packed_b(int64_t E, int64_t T, int64_t N, int64_t K,
                                            const int64_t* off, const int* tile_start,
                                            const uint16_t* A, int64_t lda, int bfmt,

@@ -96,6 +96,32 @@ def test_grouped_few_rows_per_expert(qf, wfmt, N, K):
         assert_close(dW[e].astype(np.float64), oracle.linear_dw(dY[r0:r1], X[r0:r1]), f"dW e={e}")
 
 
+@pytest.mark.parametrize("wfmt,N,K", [("nvfp4", 264, 64), ("nvfp4", 264, 192), ("nvfp4", 264, 576),
+                                      ("nvfp4", 264, 832), ("mxfp4", 264, 320), ("mxfp4", 264, 832),
+                                      ("nvfp4", 264, 80), ("mxfp4", 264, 96)])
+def test_grouped_experts_decoded_in_the_forward(qf, wfmt, N, K):
+    """100 experts of two tile columns with at most 64 rows on average and a saved NVFP4 / MXFP4
+    operand: the forward decodes the packed experts (K a multiple of 64; one stage, few stages, and
+    enough for the XCDs' rotated starts to wrap inside the loop).  Row counts around the tile
+    edges; against the form that reads W_hat, bit for bit, and against the oracle."""
+    rng = np.random.default_rng(N + K)
+    E = 100
+    counts = np.zeros(E, np.int64)
+    counts[[1, 2, 3, 4, 5, 7, 30, 63, 64, 65, 98]] = [127, 1, 128, 300, 129, 7, 256, 16, 64, 5, 33]
+    offsets = np.concatenate([[0], np.cumsum(counts)])
+    T = int(offsets[-1])
+    X = workloads.normal_bf16(rng, (T, K))
+    W = np.stack([workloads.normal_bf16(rng, (N, K), 0.02 * (e % 5 + 1)) for e in range(E)])
+    dY = workloads.normal_bf16(rng, (T, N))
+    outs = [run_grouped(qf, offsets, X, W, dY, wfmt, "none", saved=sv) for sv in (True, False)]
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+    for e in np.flatnonzero(counts):
+        r0, r1 = offsets[e], offsets[e + 1]
+        what = oracle.fakequant(W[e], wfmt)
+        assert_close(bf16_to_f64(outs[0][0][r0:r1]), oracle.linear_fwd(X[r0:r1], what), f"Y e={e}")
+
+
 @pytest.mark.parametrize("E,N,K,big", [
     (32, 2056, 64, 0),       # 9 tile columns: 288 tiles of either height, two rounds
     (32, 2048, 64, 130),     # one round of 256-row tiles, two of 128-row ones: 256
@@ -126,21 +152,20 @@ def test_grouped_tile_height_chosen_from_the_row_counts(qf, E, N, K, big):
 
 @pytest.mark.parametrize("wfmt,given", [("nvfp4", False), ("nvfp4", True), ("mxfp4", False),
                                         ("q4k", False)])
-@pytest.mark.parametrize("rows", [30, 200])
-def test_grouped_kept_workspace_after_a_forward_with_saved(qf, wfmt, given, rows):
+@pytest.mark.parametrize("E,rows", [(200, 300), (4, 30), (4, 200)])
+def test_grouped_kept_workspace_after_a_forward_with_saved(qf, wfmt, given, E, rows):
     """A backward with QF_FLAG_REUSE_WS and no saved buffer, after forwards that had one, with the
     flag in their own descriptor or not: the gradients of the backward from the saved buffer, bit
-    for bit, also where the forward decodes the packed experts (few rows) and writes no W_hat.
-    The workspace starts out as NaNs."""
+    for bit, also where the forward decodes the packed experts (200 of them with few rows) and
+    writes no W_hat.  The workspace starts out as NaNs."""
     rng = np.random.default_rng(rows)
-    E, N, K = 4, 136, 256
-    offsets = np.array([0, 0, rows, 3 * rows, 4 * rows])
-    T = 4 * rows
+    N, K, T = 136, 256, 4 * rows
+    offsets = np.array([0, 0, rows, 3 * rows] + [4 * rows] * (E - 3))
     X, dY = workloads.normal_bf16(rng, (T, K)), workloads.normal_bf16(rng, (T, N))
-    W = np.concatenate([workloads.normal_bf16(rng, (N, K), 0.02 * (e + 1)) for e in range(E)])
+    W = np.concatenate([workloads.normal_bf16(rng, (N, K), 0.02 * (e % 7 + 1)) for e in range(E)])
     g = None
     if given:
-        g = torch.tensor([0.5, 0.25, 1.0, 0.75], dtype=torch.float32, device="cuda")
+        g = torch.tensor([0.5, 0.25, 1.0, 0.75] * (E // 4), dtype=torch.float32, device="cuda")
     off = torch.from_numpy(offsets.astype(np.int64)).cuda()
     Xd, Wd, dYd = to_dev(X), to_dev(W), to_dev(dY)
     outs = []
