@@ -2,16 +2,23 @@
 
 Flags: -ffp-contract=off keeps every FP32 step of the quantizers a single IEEE operation
 (results are bit-exact across implementations); packed FP32 ops are disabled for all device
-code.  The C ABI is declared in include/qf.h at the repository root.
+code.  The C ABI is declared in include/qf.h at the repository root.  The wait states around the
+GEMM's inline-assembly MFMAs are checked in the result (mfma_check).
 """
 import glob
 import os
 import subprocess
 
+if __package__:
+    from . import mfma_check
+else:                                            # run as a script
+    import mfma_check
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libqf.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+OBJDUMP = os.environ.get("LLVM_OBJDUMP", "/opt/rocm/llvm/bin/llvm-objdump")
 ARCH = "gfx950"
 
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=" + ARCH,
@@ -36,6 +43,7 @@ def build(verbose: bool = False) -> str:
     if verbose and err.strip():
         print(err)
     check_stubs(tmp)
+    mfma_check.check_library(tmp, OBJDUMP)
     os.replace(tmp, LIB)
     return LIB
 
