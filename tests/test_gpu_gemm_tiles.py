@@ -110,3 +110,26 @@ def test_fragment_order_equals_row_order_in_256x256_tiles(qf, c32):
     qf.gemm_bf16(M, N, K, Ad, K, 1, Bd, K, 1, C2, N, c32)
     torch.cuda.synchronize()
     assert torch.equal(C1, C2)
+
+
+@pytest.mark.parametrize("M,N,K", [(2048, 2048, 1024), (2040, 2048, 1088), (1024, 2048, 1024),
+                                   (1024, 2044, 1088), (2048, 2048, 200), (1016, 2040, 136)],
+                         ids=["128x128", "128x128 odd stages", "128x64", "128x64 odd stages",
+                              "128x128 tail", "128x64 tail"])
+def test_k_halves_in_small_tiles(qf, M, N, K):
+    """FP32 with a workspace, in the small kernel's two largest tiles: the sum of the two K halves that
+    the large tiles form, so bit-identical to the fragment-order product, which runs in those."""
+    ws = qf.gemm_workspace(M, N, 1)
+    assert ws is not None
+    _check(qf, M, N, K, 1, ws=ws)
+    if K % 64:
+        return
+    A, B = _operands(M, N, K)
+    Ad, Bd = to_dev(A), to_dev(B)
+    Bf = torch.empty(qf.fragment_bytes(N, K) // 2, dtype=torch.int16, device="cuda")
+    qf.pack_fragments(Bd, Bf)
+    C1, C2 = (torch.full((M, N), v, dtype=torch.float32, device="cuda") for v in (3, 5))
+    qf.gemm_bf16_fragb(M, N, K, Ad, K, Bf, C1, N, 1, ws=ws)
+    qf.gemm_bf16(M, N, K, Ad, K, 1, Bd, K, 1, C2, N, 1, ws=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(C1, C2)

@@ -55,3 +55,34 @@ def test_ragged_token_counts(qf, M, N, K, wfmt, afmt, saved):
     ahat = oracle.fakequant(Xh, afmt, g) if afmt != "none" else Xh
     assert_close(outs[0][1].astype(np.float64), oracle.linear_dw(dYh, ahat), "dW")
     assert_close(bf16_to_f64(from_dev(outs[0][0])), oracle.linear_dx(dYh, what), "dX")
+
+
+def test_ragged_token_count_past_the_transposed_rows(qf):
+    """A ragged token count whose transposed rows are 2^22 elements and longer: the products take their
+    operands in place, stored with K as their rows.  A narrow layer, dX and dW against FP64.
+
+    dW sums 4194297 products of standard normals in FP32, about 131000 additions one after the other
+    at a running size of up to 2048: a rounding of about 2e-5 of the result's rms, well inside the
+    layer's tolerance."""
+    M, N, K = (1 << 22) - 7, 16, 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    X, dY = (torch.randn(M, c, generator=g, device="cuda").to(torch.bfloat16) for c in (K, N))
+    W = (torch.randn(N, K, generator=g, device="cuda") * 0.02).to(torch.bfloat16)
+    d = qf.qlinear_desc(M, N, K, "nvfp4", "none")
+    Y, dX = torch.empty_like(dY), torch.empty_like(X)
+    dW = torch.full((N, K), 7.0, dtype=torch.float32, device="cuda")
+    ws = qf.workspace(d)
+    ws.fill_(0xFF)
+    qf.qlinear_fwd(d, X, W, Y, ws)
+    qf.qlinear_bwd_ste(d, dY, X, W, dX, dW, ws)
+    torch.cuda.synchronize()
+    ref = torch.zeros(N, K, dtype=torch.float64, device="cuda")
+    for i in range(0, M, 1 << 19):
+        ref += dY[i:i + (1 << 19)].double().t() @ X[i:i + (1 << 19)].double()
+    assert_close(from_dev(dW).astype(np.float64), from_dev(ref), "dW")
+    what = oracle.fakequant(from_dev(W.view(torch.int16)), "nvfp4")
+    rows = np.r_[0:300, M - 300:M]
+    ri = torch.from_numpy(rows).cuda()
+    got = bf16_to_f64(from_dev(dX[ri].view(torch.int16)))
+    assert_close(got, oracle.linear_dx(from_dev(dY[ri].view(torch.int16)), what), "dX")
