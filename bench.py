@@ -737,7 +737,8 @@ def kl_row(qf, torch, dev, gen):
            "loss_only_GBps": round(n * 4.0 / (ms_loss * 1e-3) / 1e9, 1),
            "loss": round(float(loss.item()), 6),
            "work": "L=8192 tokens, V=151936, bf16 logits; algorithmic bytes 6 per element "
-                   "(two logits read, gradient written); the kernel reads the logits twice"}
+                   "(two logits read, gradient written); the part of a row that "
+                   "a compute unit does not keep is read a second time"}
     del zt, zs, grad
     torch.cuda.empty_cache()
     return out

@@ -301,7 +301,8 @@ bool fused_forward(const qf_qlinear_desc* d) {
 
 // Whether a forward with this descriptor leaves A_hat^T [K, ws_ld(M)] in the workspace (for a
 // QF_FLAG_REUSE_WS backward): the materialized forward on a token count that is a multiple of
-// 8 (the NT backward's case), with at most 32 output tile columns.  Writing A^T costs the
+// 8 (a ragged count's A_hat^T is left to the backward's transpose; writing it here has not been
+// measured), with at most 32 output tile columns.  Writing A^T costs the
 // forward GEMM a few microseconds per round of tiles plus the pieces it writes; measured at 32K
 // tokens (same box) it saves 0.18 / 0.03 / 0.01 ms net for the 4096 x 12288, 4096 x 4096 and
 // 6144 x 4096 weights (16-24 tile columns) and loses 0.06 ms for the 24576 x 4096 one (96
@@ -569,6 +570,9 @@ qf_status qf_qlinear_bwd_ste(const qf_qlinear_desc* d, const uint16_t* dY, const
   // workspace's packed region; otherwise the operands are quantized again (identical bits).
   Packed sw{}, sa{};
   if (saved) saved_layout(d, const_cast<void*>(saved), &sw, &sa);
+  // (a ragged token count quantizes W again also with QF_FLAG_REUSE_WS: unlike the forward's A_hat,
+  // its packed W is in the workspace only if the forward had no saved buffer, and this backward has
+  // always been valid after either)
   const Packed* src_w = saved ? &sw : (reuse && d->M % 8 == 0 ? &w.wpk : nullptr);
   // NT form: transposed operands through the workspace.  W_hat^T comes from the packed
   // operand (transposing dequantizer) or straight from the transposing quantizer (one pass
@@ -578,8 +582,10 @@ qf_status qf_qlinear_bwd_ste(const qf_qlinear_desc* d, const uint16_t* dY, const
   if (d->M % 8 != 0 && ldm >= kMaxNtRow) {
     // A ragged token count whose transposed rows are too long for the NT kernel's 32-bit offsets
     // within a tile: the products read W_hat [N, K], dY [M, N] and A_hat [M, K] in place, as
-    // operands stored [K'][*], through transposing LDS reads (about twice the time).  W_hat is
-    // quantized again into the workspace; A_hat is the forward's with QF_FLAG_REUSE_WS.
+    // operands stored [K'][*], through transposing LDS reads (about twice the time).  That kernel's
+    // offsets span all M rows, so it takes row strides below 256 here (narrow layers); wider ones
+    // get its error.  W_hat is quantized again into the workspace; A_hat is the forward's with
+    // QF_FLAG_REUSE_WS.
     const uint16_t *Wop, *Aop;
     int64_t ldw_op, lda_op;
     QF_TRY(quantize_operands(d, dm, X, W, w, dX != nullptr, !reuse && dW != nullptr,

@@ -11,9 +11,9 @@
 // with few rows):
 //  - 4 wavefronts, one per SIMD, each owning a 128 x 128 (128 x 64) sub-tile as 16 x 16
 //    v_mfma_f32_16x16x32_bf16 accumulators (256 / 128 AGPRs).  What bounds the full launches is
-//    power: the chip holds 1.97 GHz in a loop of these against 1.70 GHz in one of
-//    32 x 32 x 16 MFMAs, so 8192 x 14336 x 4096 takes 617 us (1.56 PFLOP/s) against 664 with the
-//    same loop built on the latter, to the same bits.
+//    power: at 8192 x 14336 x 4096 the chip holds 1.84 GHz in this loop with the MFMA pipes 80 %
+//    busy, against 1.65 GHz and 82 % with the same loop built on 32 x 32 x 16 MFMAs (counter
+//    runs), and takes 617 us (1.56 PFLOP/s) against 664, to the same bits.
 //  - K advances in 64-deep stages, double-buffered in LDS (2 x 64 KB).  A stage row is 128
 //    bytes, so every global request is a whole 128-byte cache line (32-deep stages fetch half
 //    lines and double the L2 request count).
@@ -964,18 +964,27 @@ size_t gemm_nt_split_bytes(int64_t M, int64_t N) {
 
 namespace {
 
-// Launches with at least this many stages prefetch operands into L2 (see the kernel).  Long
-// contractions read panels that no earlier round of tiles has left in the last-level cache: us,
-// without -> with, at 4096 x 4096 x 32768 841 -> 750 (FP32 out), 24576 x 4096 x 32768 4660 -> 4530
-// (FP32), 8192 x 4096 x 14336 651 -> 622, 32768 x 4096 x 6144 (writing A^T) 1144 -> 1130.  Short
-// ones find theirs there and only pay for the extra requests: 8192 x 14336 x 4096 617 -> 630.
+// Launches with at least this many stages prefetch operands into L2 (see the kernel).  What it gains
+// depends on the rounds of tiles more than on the stages: panels that an earlier round has read are
+// in the last-level cache, those of a single round come from HBM and are waited for.  Measured, us,
+// without -> with:
+//   one round, 256 x 256 tiles   4096 x 4096 x 2048 54.7 -> 54.2, x 4096 101 -> 96, x 6144 147 -> 141,
+//                                x 14336 326 -> 317, x 32768 (FP32) 940 -> 769
+//   one round, 256 x 128 tiles   2048 x 4096 x 1024 18.9 -> 20.1, x 2048 41 -> 33, x 4096 79 -> 58,
+//                                x 8192 154 -> 116
+//   two to four rounds           8192 x 4096 x 4096 193 -> 191, x 14336 660 -> 642; 14336 x 4096 x 6144
+//                                516 -> 525, x 14336 1244 -> 1232 (writing A^T 1366 -> 1276)
+//   seven rounds                 8192 x 14336 x 4096 647 -> 650, x 8192 1253 -> 1265
+// The line at 96 stages takes the long single rounds and costs the many-round launches past it 1 %;
+// single rounds of 32 to 95 stages, which would gain most, are below it.
 constexpr int64_t kPfMinStages = 96;
 
 // The tile of a dense k-contiguous product: the one whose busiest compute unit copies the fewest
 // operand bytes, ceil(tiles / units) (rows + columns), the smaller tile of equals (the figures are
 // at the top of qf_gemm_small.hip; 2048 x 4096 x 4096: 84 us in 256 x 256 tiles, 71 in 256 x 128).
-// It depends on M, N and the device alone, so every form of one product (A^T written or not, B
-// packed, in fragment order) sums in the same order.
+// For a bf16 result it depends on M, N and the device alone, so every form of one product (A^T written
+// or not, B packed, in fragment order) sums in the same order.  FP32 with a workspace that allows
+// halves, which also takes two full stages, is a choice of its own, with its own order of summation.
 // halves: FP32 output summed as two K halves; 256 x 256 tiles then run as twice as many half-length
 // items plus a pass that adds them (2048 x 2048 x 4096: 63 us, 41 in 128 x 128 tiles that add the
 // halves themselves), and the 256 x 128 tile, which does not form halves, is left out.
