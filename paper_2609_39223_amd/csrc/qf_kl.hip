@@ -26,9 +26,9 @@
 //    is replaced only when a maximum passes it: few chunks rescale (exactly, by powers of two), no
 //    exponent is above 1, and those that count have arguments of about -8 (a rounding of 2^-22); the
 //    element of a maximum is looked for once a row, and only where both maxima are in one chunk.
-// 4096 x 151936: 945 -> 784 us; 8192 x 32000: 444 -> 321; 2048 x 65536: 221 -> 169 (against one
-// workgroup per row reading it twice; keeping alone 880 / 456 / 210, with the refills 830 / 345 /
-// 193).  Each lane folds its 16-byte chunks in a fixed order and the workgroup merges the lanes'
+// 4096 x 151936: 916 -> 768 us; 8192 x 32000: 446 -> 328; 2048 x 65536: 221 -> 164 (against one
+// workgroup per row reading it twice; keeping alone 0.95 / 1.03 / 0.95 of its time, with the refills
+// 0.90 / 0.78 / 0.87).  Each lane folds its 16-byte chunks in a fixed order and the workgroup merges the lanes'
 // statistics in a fixed tree, so the results are deterministic.  The gradient goes out with
 // non-temporal stores so it does not evict the logits; a lane reads its chunks for the last time
 // before it writes their gradient.
@@ -401,12 +401,13 @@ hipError_t launch_qad_kl(const uint16_t* zt, int64_t ldt, const uint16_t* zs, in
                          uint16_t* grad, int64_t ldg, int32_t* agree, hipStream_t s) {
   if (L > 0) {
     // Two 512-lane workgroups a unit where they keep most of a row (against one of 1024, us: 8192 x
-    // 32000 328 / 416, 2048 x 49152 127 / 148, 2048 x 65536 169 / 182, 2048 x 100000 272 / 273, 4096 x
-    // 151936 863 / 797).  The same with fewer rows than units, where a unit has one of them: 16 x
-    // 16384 12.5 / 14.5, 64 x 32000 15.0 / 17.0, 256 x 32000 17.5 / 18.7, 64 x 65536 21.8 / 22.3; and
-    // without a gradient, where all four that fit run (the row kernel of one 1024-lane workgroup and
-    // a merge by one lane: 1024 x 4096 23.1, 1024 x 32000 43.3, 256 x 32000 15.0): 1024 x 4096 14.6 /
-    // 24.7, 1024 x 32000 32.3 / 41.2, 256 x 32000 12.5 / 13.4, 64 x 65536 15.8 / 15.2.
+    // 32000 328 / 413, 2048 x 49152 124 / 146, 2048 x 65536 164 / 178, 2048 x 100000 270 / 270, 8192 x
+    // 100000 1034 / 1005, 4096 x 151936 845 / 768).  The same with fewer rows than units, where a unit
+    // has one of them: 16 x 16384 12.5 / 14.5, 64 x 32000 15.0 / 17.0, 256 x 32000 17.5 / 18.7, 64 x
+    // 65536 21.8 / 22.3; and without a gradient, where all four that fit run (the row kernel of one
+    // 1024-lane workgroup and a merge by one lane: 4096 x 4096 73.6, 1024 x 32000 43.3, 256 x 32000
+    // 15.0): 1024 x 4096 14.6 / 24.7, 1024 x 32000 32.3 / 41.2, 256 x 32000 12.5 / 13.4, 64 x 65536
+    // 15.8 / 15.2, 4096 x 65536 187 / 205, 4096 x 151936 418 / 415.
     const bool wide = V > 65536;
     auto* k = wide ? (grad ? &qad_kl_kernel<1024, true> : &qad_kl_kernel<1024, false>)
                    : (grad ? &qad_kl_kernel<512, true> : &qad_kl_kernel<512, false>);
