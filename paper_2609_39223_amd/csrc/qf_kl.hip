@@ -24,12 +24,12 @@
 //    vocabularies take two 512-lane workgroups a unit, whose passes overlap.
 //  - a new reference of a lane's sums is an integer 7 to 8 above the maximum it was made from, and
 //    is replaced only when a maximum passes it: few chunks rescale (exactly, by powers of two), no
-//    exponent is above 1, and those that count have arguments of about -8 (a rounding of 2^-22); the
-//    element of a maximum is looked for once a row, and only where both maxima are in one chunk.
+//    exponential is above 1, and the arguments of those that count are about -8 (rounded to 2^-22);
+//    the element of a maximum is looked for once a row, and only where both maxima are in one chunk.
 // 4096 x 151936: 916 -> 768 us; 8192 x 32000: 446 -> 328; 2048 x 65536: 221 -> 164 (against one
 // workgroup per row reading it twice; keeping alone 0.95 / 1.03 / 0.95 of its time, with the refills
-// 0.90 / 0.78 / 0.87).  Each lane folds its 16-byte chunks in a fixed order and the workgroup merges the lanes'
-// statistics in a fixed tree, so the results are deterministic.  The gradient goes out with
+// 0.90 / 0.78 / 0.87).  Each lane folds its 16-byte chunks in a fixed order and the workgroup merges
+// the lanes' statistics in a fixed tree, so the results are deterministic.  The gradient goes out with
 // non-temporal stores so it does not evict the logits; a lane reads its chunks for the last time
 // before it writes their gradient.
 #include <hip/hip_runtime.h>

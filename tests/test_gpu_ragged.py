@@ -86,3 +86,27 @@ def test_ragged_token_count_past_the_transposed_rows(qf):
     ri = torch.from_numpy(rows).cuda()
     got = bf16_to_f64(from_dev(dX[ri].view(torch.int16)))
     assert_close(got, oracle.linear_dx(from_dev(dY[ri].view(torch.int16)), what), "dX")
+
+
+@pytest.mark.parametrize("wfmt,afmt", [("nvfp4", "none"), ("mxfp4", "mxfp4"), ("q4k", "none")])
+def test_ragged_kept_workspace_after_a_forward_with_saved(qf, wfmt, afmt):
+    """QF_FLAG_REUSE_WS and no saved buffer on a ragged token count, after a forward with one and after
+    a forward without: the gradients of the backward from the saved buffer, bit for bit.  The
+    workspace starts out as NaNs (after the former it holds no packed W)."""
+    M, N, K = 1027, 136, 512
+    rng = np.random.default_rng(1)
+    X, W = to_dev(workloads.normal_bf16(rng, (M, K))), to_dev(workloads.normal_bf16(rng, (N, K), 0.02))
+    dY = to_dev(workloads.normal_bf16(rng, (M, N)))
+    outs = []
+    for fwd_saved, bwd_saved in ((True, True), (True, False), (False, False)):
+        d = qf.qlinear_desc(M, N, K, wfmt, afmt, flags=qf.FLAG_REUSE_WS)
+        sv, ws = qf.saved_buffer(d), qf.workspace(d)
+        ws.fill_(0xFF)
+        Y, dX = empty_bf16((M, N)), empty_bf16((M, K))
+        dW = torch.full((N, K), 7.0, dtype=torch.float32, device="cuda")
+        qf.qlinear_fwd(d, X, W, Y, ws, saved=sv if fwd_saved else None)
+        qf.qlinear_bwd_ste(d, dY, X, W, dX, dW, ws, saved=sv if bwd_saved else None)
+        torch.cuda.synchronize()
+        outs.append((dX, dW))
+    for dX, dW in outs[1:]:
+        assert torch.equal(dX, outs[0][0]) and torch.equal(dW, outs[0][1])
