@@ -164,8 +164,8 @@ QF_API qf_status qf_fakequant_q4k_mse(const uint16_t* x, int64_t R, int64_t K, i
 #define QF_FLAG_DECODE_IN_GEMM 2u /* forward: decode the packed weight inside the GEMM's
                                prologue instead of writing W_hat in bf16 to the workspace and
                                running a plain bf16 GEMM (identical Y; K a multiple of 64, else
-                               the flag is ignored).  Not the default: on MI355X the decoded
-                               tiles' LDS writes cost more than the bf16 W_hat pass saves */
+                               the flag is ignored).  Not the default: on MI355X the decode
+                               between the MFMAs costs more than the bf16 W_hat pass saves */
 
 typedef struct {
     int64_t M, N, K;      /* X [M, K], W [N, K], Y [M, N]                                  */

@@ -135,21 +135,26 @@ def hazards(code):
             for i in sorted(found)]
 
 
-def check_library(path, objdump):
-    """Number of kernels checked; raises RuntimeError on a hazard or if there is none to check."""
-    checked, bad = 0, []
+def kernels(path, objdump):
+    """[(name, instructions)] of the kernels with inline-assembly MFMAs in a built library."""
+    found = []
     with tempfile.TemporaryDirectory() as tmp:
         lib = shutil.copy(path, os.path.join(tmp, "lib.so"))
         subprocess.run([objdump, "--offloading", lib], cwd=tmp, check=True, capture_output=True)
         for obj in glob.glob(os.path.join(tmp, "lib.so.*gfx950*")):
             r = subprocess.run([objdump, "-d", "--no-show-raw-insn", obj], check=True,
                                capture_output=True, text=True)
-            for name, code in parse(r.stdout).items():
-                if any(k in name for k in KERNELS) and any(c.mfma for c in code):
-                    checked += 1
-                    bad += ["%s: %s" % (name, h) for h in hazards(code)]
+            found += [(name, code) for name, code in parse(r.stdout).items()
+                      if any(k in name for k in KERNELS) and any(c.mfma for c in code)]
+    return found
+
+
+def check_library(path, objdump):
+    """Number of kernels checked; raises RuntimeError on a hazard or if there is none to check."""
+    checked = kernels(path, objdump)
+    bad = ["%s: %s" % (name, h) for name, code in checked for h in hazards(code)]
     if not checked:
         raise RuntimeError("no GEMM kernel found in %s" % path)
     if bad:
         raise RuntimeError("MFMA hazards in %s:\n%s" % (path, "\n".join(bad[:20])))
-    return checked
+    return len(checked)
