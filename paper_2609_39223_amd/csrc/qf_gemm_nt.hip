@@ -1211,24 +1211,22 @@ hipError_t launch_grouped_nt_rows(int64_t E, int64_t T, int64_t N, int64_t K, co
 
 // Few rows per expert: a weight tile is read about once, and W_hat need not be written and read
 // for that.  Forward, us, from W_hat / decoded here (128-row tiles): 64 x 16 rows, 2048 x 2048 NVFP4
-// 443 / 381, MXFP4 345 / 293; 128 x 64, 3072 x 2048 1325 / 1181 and 1042 / 959; 64 x 96, 2048 x 2048
-// 452 / 451 and 362 / 382.  Q4_K's longer decode does not pay (128 x 64: 1126 / 1186).
-// Nor does any where a few tiles decode one after another and W_hat comes back out of the 256 MB
-// last-level cache, beside W (NVFP4, us; tiles, W_hat): 8 x 2048 x 2048, 64, 67 MB 71 / 91; 8 x 3072 x
-// 2048, 96, 100 MB 91 / 105; 32 x 1024 x 1536, 128, 100 MB 87 / 96; 16 x 2560 x 1024, 160, 84 MB
-// 70 / 72.  From 128 MB on it pays from 96 tiles on (8 x 3072 x 3072, 151 MB 160 / 143; 16 x 2048 x
-// 2048, 134 MB 133 / 124), and from 192 tiles on throughout (16 x 3072 x 1024, 100 MB 80 / 78).
-// And not where 256-row tiles, in which decoding is slower, may make one round of what 128-row tiles
-// make two of: with a tile for every expert just one round, and rows enough that routing as skewed as
-// Zipf's gives an expert more than 128 of them (32 x 48 rows, 2048 x 2048: 227 / 249; 32 x 16, where
-// it does not: 218 / 193).
+// 431 / 342, MXFP4 337 / 244; 128 x 64, 3072 x 2048 1313 / 1021 and 1041 / 739.  (Also at 96 rows per
+// expert, 64 x 2048 x 2048, 454 / 380 and 367 / 279; the bound of 64 is from a slower decode.)
+// Q4_K's longer decode is not built in.
+// Not where few tiles decode one after another on an otherwise idle chip and W_hat comes back out of
+// the 256 MB last-level cache, beside W (NVFP4, 48-64 rows, us; tiles, W_hat): 16 x 768 x 2048, 48,
+// 50 MB 62 / 75; 8 x 2048 x 2048, 64, 67 MB 71 / 80; 8 x 3072 x 2048, 96, 100 MB 87 / 91.  From 128 MB
+// on it pays from 96 tiles on (8 x 3072 x 3072, 151 MB 159 / 127), and from 128 tiles on throughout
+// (16 x 2048 x 1024, 67 MB 62 / 60; 32 x 1024 x 1536, 100 MB 83 / 81; 32 x 2048 x 2048, 256 tiles
+// 247 / 205, although 256-row tiles may make one round there and 128-row tiles, the only ones that
+// decode, two).
 bool grouped_packed_b_ok(int fmt, int64_t E, int64_t T, int64_t N, int64_t K) {
   if ((fmt != QF_FMT_NVFP4 && fmt != QF_FMT_MXFP4) || K <= 0 || K % BK != 0 || T > 64 * E ||
       !nt_offsets_fit(K, K, K))
     return false;
-  const int64_t cols = (N + BN - 1) / BN, tiles = E * cols, cus = compute_units();
-  if (tiles <= cus && (E + T / 1024) * cols > cus) return false;
-  return tiles >= 192 || (tiles >= 96 && E * N * K >= (int64_t)1 << 26);
+  const int64_t tiles = E * ((N + BN - 1) / BN);
+  return tiles >= 128 || (tiles >= 96 && E * N * K >= (int64_t)1 << 26);
 }
 
 hipError_t launch_grouped_nt_rows_packed_b(int64_t E, int64_t T, int64_t N, int64_t K,
