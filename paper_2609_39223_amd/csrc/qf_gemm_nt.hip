@@ -168,7 +168,7 @@ __device__ __forceinline__ void gemm_nt_tile(const NtArgs& p, char* smem) {
   static_assert(!AT || !C_F32, "A^T output: bf16 form");
   // stage s+1's loads: L0 in the second slice of step s-1, the rest in the first of step s
   // (fragment-major B: all of A's in the latter)
-  constexpr int L0 = BF ? 0 : AT || BQ != 0 ? NLD / 2 : NLD / 4 * 3;
+  constexpr int L0 = BF ? NLD : AT || BQ != 0 ? NLD / 2 : NLD / 4 * 3;
   constexpr int CSTEP = TM == 4 ? 2 : TN / 2;    // MFMAs per copy issued
   static_assert((L0 > NLD - L0 ? L0 : NLD - L0) * CSTEP <= TM * TN, "a slice holds its copies");
   // stages between a prefetch and the stage being multiplied: us with 2 / 3 / 4, FP32 6144 x 4096
@@ -624,7 +624,9 @@ __device__ __forceinline__ void gemm_nt_tile(const NtArgs& p, char* smem) {
     constexpr int NM = TM * TN, NR = TM + TN;
     static_for<NM>([&](auto ti) __attribute__((always_inline)) {
       constexpr int t = decltype(ti)::value;
-      mfma16(acc[t / TN][t % TN], b[t % TN], a[t / TN]);
+      // (fragment-major B: by columns, so that B's registers come free one by one, see bf_hook)
+      constexpr int i = BF ? t % TM : t / TN, j = BF ? t / TM : t % TN;
+      mfma16(acc[i][j], b[j], a[i]);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (READS && t < NR) read_one(rst, rkk, t, ra, rb);
       if constexpr (LOADS && t % CSTEP == 1) {
@@ -693,9 +695,11 @@ __device__ __forceinline__ void gemm_nt_tile(const NtArgs& p, char* smem) {
     constexpr int kBqHalf = BQ == QF_FMT_NVFP4 ? 24 : BQ == QF_FMT_MXFP4 ? 12 : 23;
     constexpr int BSTEP = NM / 32;               // MFMAs per decode operation
     auto bf_hook = [&](int kk, int t) __attribute__((always_inline)) {
-      // after MFMA t = NM - TN + j, the last one using fbr[kk][j], that register is loaded with
-      // stage s+1's fragment (not in the last step)
-      if (BF && !LAST && t >= NM - TN) bf_load(e_nx1, kk, t - (NM - TN));
+      // after MFMA t = TM j + TM - 1, the last one using fbr[kk][j], that register is loaded with
+      // stage s+1's fragment (not in the last step): nearly a whole step before its next use.
+      // With all of them at the end of the slice (by rows) and A's copies in slice 0, half a
+      // step for either, 2048 x 4096 x 4096 took 85 us, this 77; 8192 x 14336 x 4096 682 / 653
+      if (BF && !LAST && t % TM == TM - 1) bf_load(e_nx1, kk, t / TM);
     };
     auto hook0 = [&](int t) __attribute__((always_inline)) {
       if (BQ != 0) {
@@ -724,10 +728,14 @@ __device__ __forceinline__ void gemm_nt_tile(const NtArgs& p, char* smem) {
     slice(std::true_type{}, std::integral_constant<bool, LD1>{}, fa[0], BF ? fbr[0] : fb[0], cs,
           1, fa[1], fb[1], e_nx1, nxt, L0, NLD - L0, hook0);
     if (BF && !LAST) {
-      // A's copies of stage s+1 and everything before them; the TN B loads issued after them in
-      // this slice stay in flight (expcnt not waited; lgkmcnt(0): this wavefront's reads of
-      // stage s are done before the barrier lets stage s+2's copies overwrite it)
-      __builtin_amdgcn_s_waitcnt(8 | (7 << 4) | (0 << 8));
+      // A's copies of stage s+1, the last of them after MFMA CSTEP (NLD - 1) + 1 of the previous
+      // step's second slice, and everything before them; the B loads issued since, that slice's
+      // last ones and this slice's TN, stay in flight (expcnt not waited; lgkmcnt(0): this
+      // wavefront's reads of stage s are done before the barrier lets stage s+2's copies
+      // overwrite it)
+      constexpr int since = TN - (CSTEP * (NLD - 1) + 1) / TM + TN;
+      static_assert(since < 16, "the wait's low field");
+      __builtin_amdgcn_s_waitcnt(since | (7 << 4) | (0 << 8));
     } else if (PFS) {
       // the three prefetches stay in flight (vmcnt(3), the rest as above)
       __builtin_amdgcn_s_waitcnt(3 | (7 << 4) | (0 << 8));

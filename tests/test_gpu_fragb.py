@@ -67,3 +67,11 @@ def test_fragb_gemm_equals_kcontiguous(qf, M, N, K, c32):
     assert np.array_equal(c1.view(view), c2.view(view))
     got = c1.astype(np.float64) if c32 else bf16_to_f64(c1)
     assert_close(got, oracle.linear_fwd(A, B), "fragb gemm")
+
+
+@pytest.mark.parametrize("c32", [0, 1])
+@pytest.mark.parametrize("stages", [3, 4, 5, 6, 7])
+def test_fragb_gemm_few_stages(qf, stages, c32):
+    """Contractions of three to seven 64-deep stages: every way through the loop's two-step body and
+    the steps after it, whose waits count the B loads under way."""
+    test_fragb_gemm_equals_kcontiguous(qf, 264, 520, 64 * stages, c32)
